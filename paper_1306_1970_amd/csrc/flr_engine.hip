@@ -88,7 +88,10 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
   D.rb1 = (int32_t)((n + D.r1 - 1) / D.r1);
   D.cb2 = (int32_t)(D.p_pad / D.c2);
   int64_t rb2 = std::max<int64_t>(1, (target_b + D.cb2 - 1) / D.cb2);
-  rb2 = std::min<int64_t>(rb2, std::max<int64_t>(1, n / 4));
+  // at least 32 rows per row panel (one batch of eight rows in flight per
+  // wave): a finer split only adds partials for the block kernel to sum
+  // (n = 1000, p = 200 f64: 128 panels 45 us per PCG step, 31 panels 19 us)
+  rb2 = std::min<int64_t>(rb2, std::max<int64_t>(1, n / 32));
   int64_t r2 = (n + rb2 - 1) / rb2;
   if (r2 > kMaxR2) r2 = kMaxR2;
   D.r2 = (int32_t)r2;
