@@ -619,6 +619,7 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   CK(dalloc(h, &B.penpart, (size_t)D.nblk));
   CK(dalloc(h, &B.blk, (size_t)BK_N * (size_t)D.nblk));
   CK(dalloc(h, &B.carry, 2 * (size_t)D.nblk));
+  CK(dalloc(h, &B.mob, 5 * (size_t)D.nblk));
   // banded factor of M for graphs of bandwidth >= 2 (lattice, all-pairs)
   {
     int64_t bw = 0;

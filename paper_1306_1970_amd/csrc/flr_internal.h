@@ -106,6 +106,7 @@ struct Bufs {
   double* penpart;  // nblk
   double* blk;      // BK_N * nblk
   double* carry;    // 2 * nblk: forward carries G, then backward carries Z
+  double* mob;      // 4 * nblk: the blocks' Moebius products, then nblk: t before each block (tridiagonal factor)
   double* Lb;       // banded Cholesky factor of M by columns, p x W (banded mode only)
   double* LbT;      // the same by rows
   double* invdb;    // 1 / L_jj

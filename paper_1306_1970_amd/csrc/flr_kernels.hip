@@ -20,7 +20,7 @@ namespace flr {
 
 // v[first * stride] + ... + v[(count - 1) * stride] in that order, eight loads
 // in flight at a time (one load per add leaves each waiting for the last:
-// k_block 35 us with 128 partials, 7 us with 31 in such batches).
+// the block kernel's launch 35 us with 128 partials, 9.3 us with 31 in such batches).
 __device__ inline double sum_parts(const double* __restrict__ v, int64_t stride, int first, int count) {
   double sum = 0.0;
   for (int q = first; q < count; q += 8) {
@@ -302,7 +302,8 @@ __device__ inline void cols_b(const Dims& D, const XT* Xb, int64_t r0, int64_t r
 // share of p^T Q p.  MM boundary: the same product for the new residual, the
 // loss partials 1/2 ||y - X b||^2, and (first nblk workgroups) reweighting
 // a_j = 1/(|b_j|+eps), w_jk = 1/(|b_j - b_k|+eps), the tridiagonal part of M,
-// the penalty sums of f, and each block's factorization product.
+// the penalty sums of f, and each block's product of the tridiagonal
+// factorization (the last block to arrive combines them).
 // ---------------------------------------------------------------------------
 template <typename XT, bool MX>
 __device__ __forceinline__ void gemv_b_body(const Dims& D, const Bufs& B, const State* __restrict__ sin,
@@ -414,7 +415,8 @@ __device__ __forceinline__ void gemv_b_body(const Dims& D, const Bufs& B, const 
 
   const bool mmb = s.phase == PH_END;  // an MM boundary (not a refinement's residual refresh)
   if (mmb && wg < D.nblk) {
-    // reweighting and the tridiagonal part of M, penalties
+    // reweighting and the tridiagonal part of M, penalties.  d: the diagonal of
+    // M (banded mode), or its part beside the couplings e_j of (j-1, j)
     const int64_t j = (int64_t)wg * kBlk + tid;
     double pen = 0.0, dj = 1.0, ej = 0.0;
     if (j < D.p) {
@@ -428,38 +430,74 @@ __device__ __forceinline__ void gemv_b_body(const Dims& D, const Bufs& B, const 
         const double dlt = fabs(xj - B.x[k]);
         const double wq = 1.0 / (dlt + prm.eps);
         B.w[q] = wq;
-        wsum += wq;
+        const bool coupled = !prm.band && !prm.jacobi && (k == j - 1 || k == j + 1);
+        if (!coupled) wsum += wq;
+        if (coupled && k == j - 1) ej = prm.lam2 * wq;
         if (k > j) pen2 += dlt;
-        if (k == j - 1 && !prm.jacobi) ej = -prm.lam2 * wq;
       }
       pen = prm.lam1 * fabs(xj) + prm.lam2 * pen2;
       dj = prm.lam1 * aj + prm.lam2 * wsum;
       if (prm.jacobi) dj += B.s[j];
+    }
+    if (j < D.p_pad) {
       B.d[j] = dj;
       B.e[j] = ej;
-    } else if (j < D.p_pad) {
-      B.d[j] = 1.0;
-      B.e[j] = 0.0;
     }
     const double tot = wg_sum(pen, sh_s);
     if (tid == 0) B.penpart[wg] = tot;
-  }
-  if (mmb) {
-    // The last workgroup to finish factors M = L D L^T over all p elements
-    // (one wave runs the pivot chain); writes L and 1/D for the C launch.
-    __shared__ int sh_flag;
-    __syncthreads();
-    if (tid == 0) {
-      __threadfence();
-      const unsigned prev = atomicAdd(B.counter + 16, 1u);
-      const bool last = prev == (unsigned)(D.gridB - 1);
-      if (last) __threadfence();
-      sh_flag = last;
-    }
-    __syncthreads();
-    if (sh_flag) {
-      if (wave == 0 && !prm.band) tri_factor_wave(B.d, B.e, B.L, B.invD, D.p, &sh_red[0][0]);
-      if (tid == 0) B.counter[16] = 0u;
+    if (!prm.band) {
+      // Tridiagonal factor: each block's Moebius product; the last of the
+      // nblk workgroups to arrive scans them to the value before each block,
+      // and the C launch scans inside the blocks.  One wave walking the p
+      // pivots here took 41 ns each: this launch was 408 us at an MM boundary
+      // with p = 10^4 and 3.9 ms with p = 10^5, now 15 and 38.
+      const int K = D.nblk;
+      const Mob mb = wg_scan_mob(mob_leaf(dj, ej), sh_s);
+      if (tid == kWG - 1) {
+        double* o = B.mob + 4 * (int64_t)wg;
+        o[0] = mb.a;
+        o[1] = mb.b;
+        o[2] = mb.c;
+        o[3] = mb.d;
+      }
+      __shared__ int sh_flag;
+      __syncthreads();
+      if (tid == kWG - 1) {  // the thread that wrote publishes
+        __threadfence();
+        const unsigned prev = atomicAdd(B.counter + 16, 1u);
+        const bool last = prev == (unsigned)(K - 1);
+        if (last) __threadfence();
+        sh_flag = last;
+      }
+      __syncthreads();
+      if (sh_flag) {
+        // thread t: blocks t e4 .. t e4 + e4 - 1
+        constexpr int EMAX = kMaxBlocks / kWG;
+        const int e4 = (K + kWG - 1) / kWG;
+        Mob bm[EMAX], pr = {1.0, 0.0, 0.0, 1.0};
+#pragma unroll
+        for (int i = 0; i < EMAX; ++i) {
+          const int k = tid * e4 + i;
+          const bool in = i < e4 && k < K;
+          const double* o = B.mob + 4 * (int64_t)(in ? k : 0);
+          bm[i] = {o[0], o[1], o[2], o[3]};
+          if (in) pr = i == 0 ? bm[0] : mob_compose(pr, bm[i]);
+        }
+        const Mob inc = wg_scan_mob(pr, sh_s);
+        // t after this thread's last block (the first element's map is constant, so any inflow gives it)
+        sh_red[0][tid] = inc.b / inc.d;
+        __syncthreads();
+        double t = tid == 0 ? 0.0 : sh_red[0][tid - 1];
+#pragma unroll
+        for (int i = 0; i < EMAX; ++i) {
+          const int k = tid * e4 + i;
+          if (i < e4 && k < K) {
+            B.mob[4 * (int64_t)K + k] = t;
+            t = mob_apply(bm[i], t);
+          }
+        }
+        if (tid == 0) B.counter[16] = 0u;
+      }
     }
   }
 }
@@ -723,9 +761,9 @@ __device__ inline bool arrive_last(const Bufs& B, int nblocks, int* flag) {
 // C: per solver block (256 elements).  PCG step: nu = r^T z / p^T Q p,
 // x += nu p, r -= nu Q p (the residual update with the minus sign), then the
 // local solve of the new residual.  MM boundary: f of the iterate, the
-// relative-change test of Algorithm 2, and - if continuing - the LDL^T
-// factorization of the tridiagonal M (carry of the block products, then the
-// block's own continued fraction), the gain vectors, r0 = c - Q x0 and its
+// relative-change test of Algorithm 2, and - if continuing - the block's part
+// of the LDL^T factorization of the tridiagonal M (a scan from the value that
+// the B launch left for it), the gain vectors, r0 = c - Q x0 and its
 // local solve.  The last workgroup to finish combines the blocks.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const State* __restrict__ sin,
@@ -817,16 +855,12 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   }
 
   // ---- MM boundary, or an FP64 residual refresh (refinement) ----
-  // inputs that do not depend on the decision, loaded up front (L and 1/D come
-  // from the sequential factorization at the end of the B launch)
-  double cj = 0.0, qsum = 0.0, Lj = 0.0, invDj = 0.0, Lnb = 0.0;
+  // inputs that do not depend on the decision, loaded up front
+  double cj = 0.0, qsum = 0.0;
   if (real) {
     cj = B.c[j];
-    Lj = B.L[j];
-    invDj = B.invD[j];
     qsum = sum_parts(B.qpart + j, D.p_pad, 0, D.rb2);
   }
-  if (tid == 0) Lnb = (j + kBlk < D.p) ? B.L[j + kBlk] : 0.0;
   if (s.phase == PH_RES) {
     // true residual c - (X^T X + M) x of this MM step's system, in FP64 (the
     // weights and the factorization of M are the ones the PCG used)
@@ -844,8 +878,9 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
       return;
     }
     const double sigj = real ? B.sig[j] : 0.0, psij = real ? B.psi[j] : 0.0;
+    const double Lj = real ? B.L[j] : 0.0, invDj = real ? B.invD[j] : 0.0;
     sh_L[tid] = Lj;
-    if (tid == 0) sh_L[kBlk] = Lnb;
+    if (tid == 0) sh_L[kBlk] = (j + kBlk < D.p) ? B.L[j + kBlk] : 0.0;
     __syncthreads();
     block_local_solve(D, B, b, j, rj, Lj, sh_L[tid + 1], invDj, sigj, psij, lds, lds2);
     if (arrive_last(B, D.nblk, &sh_flag)) {
@@ -901,10 +936,19 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
     }
     return;
   }
-  sh_L[tid] = Lj;
-  if (tid == 0) sh_L[kBlk] = Lnb;
+  // L and 1/D of this block: scan of its Moebius maps from t before the block
+  // (past p: d = 1, e = 0)
+  const bool inpad = j < D.p_pad;
+  const double alj = inpad ? B.d[j] : 1.0, ej = inpad ? B.e[j] : 0.0;
+  const double en = j + 1 < D.p ? B.e[j + 1] : 0.0;
+  const double tin = B.mob[4 * (int64_t)D.nblk + b];
+  const double tj = mob_apply(wg_scan_mob(mob_leaf(alj, ej), lds), tin);
+  const double invDj = real ? 1.0 / (tj + en) : 0.0;
+  const double Lnext = real ? -en * invDj : 0.0;
+  sh_L[tid + 1] = Lnext;
+  if (tid == 0) sh_L[0] = ej > 0.0 ? -ej / (tin + ej) : 0.0;
   __syncthreads();
-  const double Lnext = sh_L[tid + 1];
+  const double Lj = real ? sh_L[tid] : 0.0;
   // phi_j = prod_{i=start..j} (-L_i); psi_j = prod_{i=j+1..end+1} (-L_i);
   // sigma = zero-inflow backward sweep of phi / D
   const double phi = wg_scan_fwd({-Lj, 0.0}, lds).a;
