@@ -613,7 +613,7 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   CK(dalloc(h, &B.sig, (size_t)D.p_pad));
   CK(dalloc(h, &B.psi, (size_t)D.p_pad));
   CK(dalloc(h, &B.upart, (size_t)D.cb1 * (size_t)n));
-  CK(dalloc(h, &B.qpart, (size_t)D.rb2 * (size_t)D.p_pad));
+  CK(dalloc(h, &B.qpart, 2 * (size_t)D.rb2 * (size_t)D.p_pad));  // the setup uses two such arrays
   CK(dalloc(h, &B.pqpart, (size_t)D.gridB));
   CK(dalloc(h, &B.losspart, (size_t)std::max(D.rb2, D.cb2)));
   CK(dalloc(h, &B.penpart, (size_t)D.nblk));
@@ -652,16 +652,12 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   std::vector<double> hc((size_t)D.p);
   if (!flsa) {
     CK(launch_check_finite(Xd, x_dtype, (int64_t)n * D.ldx, flag, h->stream));
-    // setup partials reuse the q/u work areas: qpart holds rb2 x p_pad doubles
     cpart = B.qpart;
-    double* tmp2 = nullptr;
-    CK(hipMalloc(reinterpret_cast<void**>(&tmp2), (size_t)D.rb2 * (size_t)D.p_pad * sizeof(double)));
-    spart = tmp2;
+    spart = B.qpart + (size_t)D.rb2 * (size_t)D.p_pad;
     CK(launch_setup(D, Xd, yd, cpart, spart, c, s, h->stream));
     CK(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     CK(hipMemcpyAsync(hc.data(), c, (size_t)D.p * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     CK(hipStreamSynchronize(h->stream));
-    (void)hipFree(tmp2);
   } else {
     // X = I: c = X^T y = y, ||X_j||^2 = 1 (the padding keeps zeros from dalloc)
     std::vector<double> ones((size_t)D.p, 1.0);
