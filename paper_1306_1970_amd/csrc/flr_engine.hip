@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -15,10 +16,12 @@
 #include "../../include/flr.h"
 #include "flr_band.h"
 #include "flr_internal.h"
+#include "flr_nest.h"
 #include "flr_problem.h"
 
 namespace flr {
-hipError_t launch_rotation(const Dims& D, const Bufs& B, int par, int which, hipStream_t st, bool mixed);
+hipError_t launch_rotation(const Dims& D, const Bufs& B, const GroupEntry* self, int par, int which, hipStream_t st,
+                           bool mixed);
 hipError_t launch_setup(const Dims& D, const void* X, const double* y, double* cpart, double* spart, double* c,
                         double* s, hipStream_t st);
 hipError_t launch_init(const Dims& D, const Bufs& B, const double* warm, int use_warm, hipStream_t st);
@@ -108,6 +111,70 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
   return D;
 }
 
+// How a banded M (bandwidth bw) of order p is cut for the nested inverses
+// (flr_nest.h): the S with the least time for a typical MM iteration, one
+// factorization and 40 applies.  The model, in us, from measured launches:
+// an apply costs its bytes at 4.5 TB/s and 3 (S = 1) or 9 (three launches); a
+// stage 14 (the inversion of the next pivot block) or its tiles at 3.4 us of
+// matrix-core time per CU.  Small orders stay whole (S = 1 up to p of about
+// 1500); 100 x 100 gives S = 15, 128 x 128 S = 19.  S = 0, the band factor in
+// one workgroup instead, where the matrices pass 4 GB (the band factor's own
+// limit) or a segment the LDS.
+Nest nest_plan(int64_t p, int64_t bw) {
+  Nest best{};
+  double best_cost = 0.0;
+  for (int64_t S = 1; S <= 128; ++S) {
+    const int64_t m = S == 1 ? p : (p - (S - 1) * bw + S - 1) / S;
+    if (S > 1 && m < bw) break;
+    if (p - (S - 1) * (m + bw) < 1) continue;
+    const int64_t nt = (S - 1) * bw, mt = (m + kTile - 1) / kTile, bt = S == 1 ? 0 : (2 * bw + kTile - 1) / kTile;
+    const int64_t tt = (nt + kTile - 1) / kTile, N = kTile * (mt + bt), ntp = kTile * tt;
+    if (m > kNestLds - kNT || nt > kNestLds - kNT) continue;
+    const int64_t pans = std::max(S * (mt + bt), tt);
+    const double mem = 8.0 * ((double)S * N * N + (double)ntp * ntp + 2.0 * (pans + S) * kTE);
+    if (mem > 4.0 * (1 << 30)) continue;
+    const double tiles = (double)S * (mt + bt) * (mt + bt + 1) / 2, ttiles = (double)tt * (tt + 1) / 2;
+    const double apply = S == 1 ? 3.0 + 8e-6 / 4.5 * p * p
+                                : 9.0 + 8e-6 / 4.5 * ((double)S * m * (m + 4 * bw) + (double)nt * nt);
+    const double factor = (1 + mt) * std::max(14.0, 6.0 + 0.6 * 3.4 / 256 * tiles) +
+                          (S == 1 ? 0.0 : (1 + tt) * std::max(14.0, 6.0 + 3.4 / 256 * ttiles));
+    const double cost = 40.0 * apply + factor;
+    if (best.S && cost >= best_cost) continue;
+    best_cost = cost;
+    best.S = (int32_t)S;
+    best.m = (int32_t)m;
+    best.bw = (int32_t)bw;
+    best.mt = (int32_t)mt;
+    best.bt = (int32_t)bt;
+    best.N = (int32_t)N;
+    best.nt = (int32_t)nt;
+    best.tt = (int32_t)tt;
+    best.ntp = (int32_t)ntp;
+    best.pans = (int32_t)pans;
+    best.stages = (int32_t)(1 + mt + (S == 1 ? 0 : 1 + tt));
+    // 16 columns per workgroup (128-byte rows) until 32 fill the chip twice
+    best.cols = S * N / 32 >= 512 ? 32 : 16;
+    const int64_t widest = std::max({(int64_t)tiles, (int64_t)ttiles, S * N / best.cols, ntp / kTopCols});
+    best.wgs = (int32_t)std::min<int64_t>(512, widest);  // two per CU
+    best.nparts = (int32_t)(S == 1 ? N / best.cols : ntp / kTopCols + S * (kTile * mt / best.cols));
+  }
+  return best;
+}
+
+// Launches of one round of the rotation (Launch values), by how M is applied.
+std::vector<int> round_launches(bool factor, bool nest, bool nest_tops) {
+  std::vector<int> v = {LN_A, LN_B, LN_C};
+  if (factor) v.push_back(LN_BAND);
+  if (nest) v.push_back(LN_NEST1);
+  if (nest_tops) v.insert(v.end(), {LN_NEST2, LN_NEST3});
+  if (nest) v.push_back(LN_NEST4);
+  return v;
+}
+
+BandMode band_mode(flr_problem h) {
+  return !h->h_prm->band ? BAND_NONE : h->B.nest.S ? BAND_NEST : BAND_FACTOR;
+}
+
 bool is_device_ptr(const void* ptr) {
   hipPointerAttribute_t attr;
   if (hipPointerGetAttributes(&attr, ptr) != hipSuccess) {
@@ -123,9 +190,11 @@ flr_status build_graph(flr_problem h, bool mixed, bool band) {
   if (ge) return FLR_OK;
   HIP_OR_FAIL(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
   hipError_t err = hipSuccess;
-  const int per = band ? 4 : 3;  // A, B, C (, K)
+  const int S = h->B.nest.S;
+  const std::vector<int> round = round_launches(band && !S, band && S, band && S > 1);
+  const int per = (int)round.size();
   for (int i = 0; i < per * kRounds && err == hipSuccess; ++i)
-    err = launch_rotation(h->D, h->B, i & 1, i % per, h->stream, mixed);
+    err = launch_rotation(h->D, h->B, h->d_self, i & 1, round[(size_t)(i % per)], h->stream, mixed);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(h->stream, &g);
   if (err != hipSuccess) return fail(FLR_ERR_DEVICE, std::string("capture launch: ") + hipGetErrorString(err));
@@ -203,8 +272,9 @@ flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const 
   HIP_OR_FAIL(launch_init(D, h->B, warm, use_warm, h->stream));
   // every MM step takes at most max_cg PCG steps, as many FP64 residual
   // refreshes (mixed precision: each follows at least one PCG step) and its
-  // boundary; one graph launch holds kRounds rotations
-  run.max_launches = ((int64_t)P.max_iter * (2 * (int64_t)P.max_cg + 2) + 2) / kRounds + 4;
+  // boundary (with nested inverses, a factorization of at least one stage per
+  // round); one graph launch holds kRounds rotations
+  run.max_launches = ((int64_t)P.max_iter * (2 * (int64_t)P.max_cg + 2 + h->B.nest.stages) + 2) / kRounds + 4;
   run.launched = 0;
   run.in_flight = 0;
   run.done = false;
@@ -327,9 +397,9 @@ struct BatchWork {
 
 // The ragged batch in grouped launches: the problems are sorted into groups
 // of one stored type and precision; one round is, per group, one launch each
-// of A, B and C over every problem of the group and one banded-solve launch
-// (the problems without a band only pass their state on, which keeps every
-// problem's state parity that of the banded rotation).  kRounds rounds are
+// of A, B and C over every problem of the group and of the banded-solve
+// launches that any of them needs (the others only pass their state on, which
+// keeps the state parity of every problem of the group the same).  kRounds rounds are
 // captured in one graph on the first problem's stream and launched with two
 // in flight, the states of all problems gathered into one copy per launch;
 // the batch ends when every problem's state says done.
@@ -337,7 +407,10 @@ flr_status batch_run(const flr_problem* hs, int32_t count, std::vector<SolveRun>
   struct Group {
     int dtype;
     bool mixed;
-    int first, count, wa, wb, wc;
+    int first, count, wa, wb, wc, wk;
+    bool modes[3];  // BandMode values present
+    bool tops;      // nested inverses with separators present
+    int launches;   // done so far (state parity)
   };
   std::vector<GroupEntry> ents;
   std::vector<Group> groups;
@@ -345,7 +418,7 @@ flr_status batch_run(const flr_problem* hs, int32_t count, std::vector<SolveRun>
   int64_t max_launches = 0;
   for (int dt = 0; dt < 3; ++dt) {
     for (int mx = 0; mx < 2; ++mx) {
-      Group g{dt, mx != 0, (int)ents.size(), 0, 0, 0, 0};
+      Group g{dt, mx != 0, (int)ents.size(), 0, 0, 0, 0, 0, {false, false, false}, false, 0};
       for (int32_t i = 0; i < count; ++i) {
         flr_problem h = hs[i];
         if (h->D.dtype != dt || (h->h_prm->mixed != 0) != (mx != 0)) continue;
@@ -355,7 +428,12 @@ flr_status batch_run(const flr_problem* hs, int32_t count, std::vector<SolveRun>
         e.wg_a = g.wa;
         e.wg_b = g.wb;
         e.wg_c = g.wc;
-        e.band = h->h_prm->band != 0 ? 1 : 0;
+        e.wg_k = g.wk;
+        e.band = band_mode(h);
+        e.wgs_k = e.band == BAND_NEST ? h->B.nest.wgs : 1;
+        g.wk += e.wgs_k;
+        g.modes[e.band] = true;
+        g.tops = g.tops || (e.band == BAND_NEST && h->B.nest.S > 1);
         g.wa += h->D.cb1 * h->D.rb1;
         g.wb += h->D.gridB;
         g.wc += h->D.nblk;
@@ -382,10 +460,11 @@ flr_status batch_run(const flr_problem* hs, int32_t count, std::vector<SolveRun>
   HIP_OR_FAIL(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   hipError_t err = hipSuccess;
   for (int r = 0; r < kRounds && err == hipSuccess; ++r)
-    for (const Group& g : groups)
-      for (int which = 0; which < 4 && err == hipSuccess; ++which) {
-        const int wgs = which == 0 ? g.wa : which == 1 ? g.wb : which == 2 ? g.wc : g.count;
-        err = launch_grouped(g.dtype, g.mixed, bw.d_ent + g.first, g.count, wgs, which & 1, which, st);
+    for (Group& g : groups)
+      for (int which : round_launches(g.modes[BAND_FACTOR], g.modes[BAND_NEST], g.tops)) {
+        if (err != hipSuccess) break;
+        const int wgs = which == LN_A ? g.wa : which == LN_B ? g.wb : which == LN_C ? g.wc : g.wk;
+        err = launch_grouped(g.dtype, g.mixed, bw.d_ent + g.first, g.count, wgs, g.launches++ & 1, which, st);
       }
   hipError_t e2 = hipStreamEndCapture(st, &bw.graph);
   if (err != hipSuccess) return fail(FLR_ERR_DEVICE, std::string("batch capture: ") + hipGetErrorString(err));
@@ -620,15 +699,26 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   CK(dalloc(h, &B.blk, (size_t)BK_N * (size_t)D.nblk));
   CK(dalloc(h, &B.carry, 2 * (size_t)D.nblk));
   CK(dalloc(h, &B.mob, 5 * (size_t)D.nblk));
-  // banded factor of M for graphs of bandwidth >= 2 (lattice, all-pairs)
+  // M^-1 for graphs of bandwidth >= 2 (lattice, all-pairs)
   {
     int64_t bw = 0;
     for (auto& e : ev) bw = std::max(bw, e.second - e.first);
     const int64_t W = bw + 1;
     if (bw >= 2 && W <= kBandMaxW && (double)p * (double)W * 8.0 <= 4.0 * (1 << 30)) {
-      CK(dalloc(h, &B.Lb, (size_t)p * (size_t)W));
-      CK(dalloc(h, &B.LbT, (size_t)p * (size_t)W));
-      CK(dalloc(h, &B.invdb, (size_t)D.p_pad));
+      B.nest = nest_plan(p, bw);
+      Nest& Q = B.nest;
+      if (Q.S) {
+        CK(dalloc(h, &Q.seg, (size_t)Q.S * (size_t)Q.N * (size_t)Q.N));
+        CK(dalloc(h, &Q.top, (size_t)Q.ntp * (size_t)Q.ntp));
+        CK(dalloc(h, &Q.pan, 2 * (size_t)Q.pans * kTE));
+        CK(dalloc(h, &Q.dinv, 2 * (size_t)Q.S * kTE));
+        CK(dalloc(h, &Q.gpart, (size_t)Q.S * (size_t)Q.bt * kTile));
+        CK(dalloc(h, &Q.part, 2 * (size_t)Q.nparts));
+      } else {
+        CK(dalloc(h, &B.Lb, (size_t)p * (size_t)W));
+        CK(dalloc(h, &B.LbT, (size_t)p * (size_t)W));
+        CK(dalloc(h, &B.invdb, (size_t)D.p_pad));
+      }
       CK(dalloc(h, &B.btmp, (size_t)D.p_pad));
       h->band_w = (int)W;
     }
@@ -644,6 +734,16 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   B.c = c;
   B.s = s;
   B.prm = h->d_prm;
+  if (B.nest.S) {
+    CK(dalloc(h, &h->d_self, 1));
+    GroupEntry self{};
+    self.D = D;
+    self.B = B;
+    self.wgs_k = B.nest.wgs;
+    self.band = BAND_NEST;
+    CK(hipMemcpyAsync(h->d_self, &self, sizeof(self), hipMemcpyHostToDevice, h->stream));
+    CK(hipStreamSynchronize(h->stream));  // the copy's source goes out of scope
+  }
   CK(hipMemcpyAsync(yd, y, (size_t)n * sizeof(double), hipMemcpyHostToDevice, h->stream));
   CK(hipMemcpyAsync(rp, rowptr.data(), rowptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
   CK(hipMemcpyAsync(cl, col.data(), col.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
@@ -838,7 +938,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   HIP_OR_FAIL(hipEventCreate(&e2));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 0, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 0, 0, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
@@ -846,14 +946,14 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   float ms_a = 0.f;
   // re-time A from its own start event
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 0, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 0, 0, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   HIP_OR_FAIL(hipEventElapsedTime(&ms_a, e0, e1));
   float ms_b = 0.f;
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 1, 1, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 1, 1, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e2, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   HIP_OR_FAIL(hipEventElapsedTime(&ms_b, e1, e2));
@@ -867,7 +967,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   float ms_c = 0.f;
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 2, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 0, 2, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e2, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.x, save, vb, hipMemcpyDeviceToDevice, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.r, save + h->D.p_pad, vb, hipMemcpyDeviceToDevice, h->stream));

@@ -2,8 +2,9 @@
 //
 // One solve is a device-resident state machine.  Every launch is one of three
 // kernels that run in a fixed rotation A, B, C (a hipGraph holds S rounds);
-// when M is banded with bandwidth >= 2 a fourth, K, applies M^-1 through its
-// banded Cholesky factor after C:
+// when M is banded with bandwidth >= 2 further launches after C apply M^-1: K1
+// to K4 through nested dense inverses (flr_nest.h), or K through its banded
+// Cholesky factor (flr_band.h) where those would need too much memory:
 //   A  row-panel GEMV   u = X v            (v = new CG direction, or the MM iterate)
 //   B  column-panel GEMV q = X^T u (+ M v)  (plus, at an MM boundary: objective
 //                                            partials, reweighting, factorization products)
@@ -25,14 +26,19 @@ constexpr int kMaxC1 = 2048;      // max columns of an A tile
 constexpr int kMaxR2 = 1024;      // max rows of a B tile
 constexpr int kMaxBlocks = 1024;  // max solver blocks -> p_pad <= 262144
 
-// PH_BANDMM: an MM step goes on and M is banded (bandwidth >= 2): the fourth
-// launch of the rotation factors M and solves with the new residual.
+// PH_BANDMM: an MM step goes on and M is banded (bandwidth >= 2): the K launch
+// factors M and solves with the new residual; the launches K1..K3 do one stage
+// of the factorization each until it is complete, then K1 starts the solve
+// (PH_BANDSOLVE).
 // PH_RES (mixed precision): the inner PCG with FP32 products has met its
 // tolerance on its recursive residual; the next rotation recomputes the true
 // residual c - Q x in FP64 at the same weights and either ends the MM step
 // or restarts the PCG from it (iterative refinement).  PH_BANDRES: the same
 // refreshed residual solved through the existing banded factor.
-enum Phase : int32_t { PH_CG = 0, PH_END = 1, PH_DONE = 2, PH_BANDMM = 3, PH_RES = 4, PH_BANDRES = 5 };
+enum Phase : int32_t { PH_CG = 0, PH_END = 1, PH_DONE = 2, PH_BANDMM = 3, PH_RES = 4, PH_BANDRES = 5, PH_BANDSOLVE = 6 };
+
+// Launches of a rotation, in their order within a round.
+enum Launch : int { LN_A = 0, LN_B = 1, LN_C = 2, LN_BAND = 3, LN_NEST1 = 4, LN_NEST2 = 5, LN_NEST3 = 6, LN_NEST4 = 7 };
 
 // What a combine of the block scalars follows: a PCG step, the first residual
 // of an MM step, or a residual refreshed in FP64 (refinement).
@@ -66,6 +72,7 @@ struct State {
   int64_t cg_total;
   double rz, f_old, f_new, rel_change, rel_res, nu, gamma;
   double rres;  // relative FP64 residual at the last MM boundary or refresh (mixed precision)
+  int32_t fstage, pad;  // PH_BANDMM with nested inverses: factorization stages done
 };
 
 struct Dims {
@@ -77,6 +84,27 @@ struct Dims {
   int32_t gridB;          // max(cb2*rb2, nblk)
   int32_t flsa;           // 1: X = I (fused lasso signal approximation), no X is stored or read
   int32_t nloss;          // loss partials the block kernel sums (rb2, or cb2 when X = I)
+};
+
+// Nested dense inverses of a banded M (flr_nest.h): S segments of m indexes
+// (the last one shorter) with separators of bw between them.
+struct Nest {
+  int32_t S;        // 0: not used
+  int32_t m, bw;
+  int32_t mt, bt;   // 64-wide tiles of a segment's interior and of its two separators
+  int32_t N;        // order of a bordered segment matrix, 64 (mt + bt)
+  int32_t nt, tt, ntp;  // separator indexes (S - 1) bw, their tiles, 64 tt
+  int32_t stages;   // launches of one factorization
+  int32_t pans;     // tiles of one panel buffer
+  int32_t cols;     // columns per workgroup of the segment products (16 or 32)
+  int32_t wgs;      // workgroups of the K1..K3 launches
+  int32_t nparts;   // shares of r^T z and r^T r
+  double* seg;      // S matrices N x N
+  double* top;      // ntp x ntp
+  double* pan;      // 2 x pans tiles: the pivot column of this stage and of the next
+  double* dinv;     // 2 x S tiles: their inverted pivot blocks
+  double* gpart;    // S x 64 bt: W^T r of each segment
+  double* part;     // 2 x nparts
 };
 
 struct Bufs {
@@ -114,17 +142,20 @@ struct Bufs {
   unsigned* counter;// blocks of the current C launch that have finished
   State* st;        // 2
   const Params* prm;
+  Nest nest;
 };
 
 // One problem of a grouped launch (the ragged batch): its sizes and buffers,
-// the first workgroup of its share of the grouped A, B and C launches, and
-// whether its M is applied through the banded factor (one workgroup of the
-// grouped band launch; the other problems' workgroup only passes the state on).
+// the first workgroup of its share of the grouped A, B, C and K1..K3 launches,
+// and how its M is applied (a problem that takes no part in a launch has one
+// workgroup there, which only passes the state on).
+enum BandMode : int32_t { BAND_NONE = 0, BAND_FACTOR = 1, BAND_NEST = 2 };
 struct GroupEntry {
   Dims D;
   Bufs B;
-  int32_t wg_a, wg_b, wg_c;
-  int32_t band;
+  int32_t wg_a, wg_b, wg_c, wg_k;
+  int32_t wgs_k;
+  int32_t band;  // BandMode
 };
 
 }  // namespace flr

@@ -15,6 +15,7 @@
 #include "flr_device.h"
 #include "flr_band.h"
 #include "flr_internal.h"
+#include "flr_nest.h"
 
 namespace flr {
 
@@ -110,6 +111,8 @@ __global__ __launch_bounds__(kWG) void k_init(Dims D, Bufs B, const double* __re
     s.nu = 0.0;
     s.gamma = 0.0;
     s.rres = 0.0;
+    s.fstage = 0;
+    s.pad = 0;
     B.st[0] = s;
     B.st[1] = s;
   }
@@ -168,6 +171,9 @@ __device__ inline void rows_a(const Dims& D, const Bufs& B, const XT* Xb, int cb
   }
 }
 
+// Nothing to do for A, B and C: done, or M is being factored by later launches.
+__device__ inline bool idle(const State& s) { return s.phase == PH_DONE || s.phase == PH_BANDMM; }
+
 // ---------------------------------------------------------------------------
 // A: row-panel GEMV u_part[cb] = X[rb, cb] v[cb].  In a PCG step v is the new
 // direction p = z + gamma p_old, where z = M^-1 r is rebuilt from the local
@@ -186,7 +192,7 @@ __device__ __forceinline__ void gemv_a_body(const Dims& D, const Bufs& B, const 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cb = wg % D.cb1, rb = wg / D.cb1;
   if (wg == 0 && tid == 0) *sout = s;
-  if (s.phase == PH_DONE) return;
+  if (idle(s)) return;
   const int64_t c0 = (int64_t)cb * D.c1;
   const int64_t r0 = (int64_t)rb * D.r1, r1 = min<int64_t>(D.n, r0 + D.r1);
   const XT* Xb = reinterpret_cast<const XT*>(B.X);
@@ -315,7 +321,7 @@ __device__ __forceinline__ void gemv_b_body(const Dims& D, const Bufs& B, const 
   const State s = *sin;
   const int tid = threadIdx.x;
   if (wg == 0 && tid == 0) *sout = s;
-  if (s.phase == PH_DONE) return;
+  if (idle(s)) return;
   const int lane = tid & 63, wave = tid >> 6;
   const int ngemm = D.cb2 * D.rb2;
   const int cb = wg % D.cb2, rb = wg / D.cb2;
@@ -772,7 +778,7 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   constexpr int QMAX = 16;  // row panels whose partial products are prefetched
   const State s = *sin;
   const int tid = threadIdx.x;
-  if (s.phase == PH_DONE) {
+  if (idle(s)) {
     if (b == 0 && tid == 0) *sout = s;
     return;
   }
@@ -826,7 +832,7 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
       rj = fma(-nu, q, rj0);
       B.r[j] = rj;
     }
-    if (prm.band) {  // the K launch solves with the new residual
+    if (prm.band) {  // the K launches solve with the new residual
       if (b == 0 && tid == 0) {
         State o = s;
         o.cg_iter = s.cg_iter + 1;
@@ -869,7 +875,7 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
       rj = cj - (qsum + apply_m(B, prm, j, B.x));
       B.r[j] = rj;
     }
-    if (prm.band) {  // the K launch solves with the existing factor
+    if (prm.band) {  // the K launches solve with the existing factor
       if (b == 0 && tid == 0) {
         State o = s;
         o.phase = PH_BANDRES;
@@ -928,10 +934,12 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   o.f_old = f_new;
   o.first_cg = 1;
   o.cg_iter = 0;
-  if (prm.band) {  // r0 = c - (X^T X + M) x0; the K launch factors M and solves
+  if (prm.band) {  // r0 = c - (X^T X + M) x0; the K launches factor M and solve
     if (real) B.r[j] = cj - (qsum + apply_m(B, prm, j, B.x));
     if (b == 0 && tid == 0) {
+      B.counter[32] = 0u;  // failed pivot
       o.phase = PH_BANDMM;
+      o.fstage = 0;
       *sout = o;
     }
     return;
@@ -1051,6 +1059,94 @@ __global__ __launch_bounds__(kWG) void k_band(Dims D, Bufs B, const State* __res
 }
 
 // ---------------------------------------------------------------------------
+// K1..K4 (banded M through nested inverses, flr_nest.h).  In the factorization
+// phase each of K1..K3 does the next stage; with all stages done K1 starts the
+// solve for the new residual.  K4 sums r^T z and r^T r and takes the inner
+// stopping test and gamma, as K does.
+// ---------------------------------------------------------------------------
+template <int WHICH>
+__device__ __forceinline__ void nest_body(const NestView& B, const State* __restrict__ sin, State* __restrict__ sout,
+                                          const Params* __restrict__ prmp, const int wg) {
+  __shared__ __align__(32) double lds[kNestLds];
+  State s = *sin;
+  // the same in every lane, and said so: the tile loop's control flow and
+  // addresses depend on it (as vector values they spill 140 registers)
+  s.phase = __builtin_amdgcn_readfirstlane(s.phase);
+  s.fstage = __builtin_amdgcn_readfirstlane(s.fstage);
+  const bool lead = wg == 0 && threadIdx.x == 0;
+  if (s.phase == PH_BANDMM) {
+    if (s.fstage < B.nest.stages) {
+      if (lead) {
+        State o = s;
+        o.fstage = s.fstage + 1;
+        *sout = o;
+      }
+      nest_stage(B, prmp->lam2, s.fstage, wg, lds);
+      return;
+    }
+    if (WHICH != LN_NEST1 || B.counter[32]) {  // the solve starts at K1; a failed pivot ends it all
+      if (lead) {
+        State o = s;
+        if (WHICH == LN_NEST1) {
+          o.phase = PH_DONE;
+          o.status = ST_NUMERICAL;
+        }
+        *sout = o;
+      }
+      return;
+    }
+  }
+  if (lead) {
+    State o = s;
+    if (s.phase == PH_BANDMM) o.phase = PH_BANDSOLVE;
+    *sout = o;
+  }
+  if (s.phase == PH_DONE || s.phase == PH_END || s.phase == PH_RES) return;
+  if (WHICH == LN_NEST1) {
+    if (B.nest.cols == 16)
+      nest_apply_segments<16>(B, wg, lds);
+    else
+      nest_apply_segments<32>(B, wg, lds);
+  } else if (WHICH == LN_NEST2) {
+    if (B.nest.S > 1) nest_apply_top(B, wg, lds);
+  } else if (B.nest.S > 1) {
+    if (B.nest.cols == 16)
+      nest_apply_back<16>(B, wg, lds);
+    else
+      nest_apply_back<32>(B, wg, lds);
+  }
+}
+
+__device__ __forceinline__ void nest_finish(const Bufs& B, const State* __restrict__ sin, State* __restrict__ sout,
+                                            const Params* __restrict__ prmp) {
+  __shared__ double red[24];
+  const State s = *sin;
+  const int tid = threadIdx.x;
+  if (s.phase != PH_CG && s.phase != PH_BANDSOLVE && s.phase != PH_BANDRES) {
+    if (tid == 0) *sout = s;
+    return;
+  }
+  double rzp = 0.0, rrp = 0.0;
+  for (int q = tid; q < B.nest.nparts; q += kWG) {
+    rzp += B.nest.part[2 * q];
+    rrp += B.nest.part[2 * q + 1];
+  }
+  double sums[4] = {rzp, rrp, 0.0, 0.0};
+  wg_sum4(sums, red);
+  if (tid == 0) {
+    const Params prm = *prmp;
+    State o = s;
+    const double rz = sums[0], rn = sqrt(sums[1]) / prm.cnorm;
+    const int mode = s.phase == PH_BANDSOLVE ? CM_FIRST : s.phase == PH_BANDRES ? CM_REFRESH : CM_STEP;
+    o.phase = next_phase(prm, o, mode, sums[1], rn);
+    o.rel_res = rn;
+    o.gamma = mode != CM_STEP ? 0.0 : rz / s.rz;
+    o.rz = rz;
+    *sout = o;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // launch wrappers
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
@@ -1064,7 +1160,10 @@ __device__ inline int group_of(const GroupEntry* __restrict__ e, int count, int 
   int lo = 0, hi = count - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    const int start = which == 0 ? e[mid].wg_a : which == 1 ? e[mid].wg_b : e[mid].wg_c;
+    const int start = which == LN_A   ? e[mid].wg_a
+                      : which == LN_B ? e[mid].wg_b
+                      : which == LN_C ? e[mid].wg_c
+                                      : e[mid].wg_k;
     if (start <= wg) lo = mid;
     else hi = mid - 1;
   }
@@ -1073,28 +1172,54 @@ __device__ inline int group_of(const GroupEntry* __restrict__ e, int count, int 
 
 template <typename XT, bool MX>
 __global__ __launch_bounds__(kWG) void k_gemv_a_grp(const GroupEntry* __restrict__ e, int count, int par) {
-  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, 0)];
+  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, LN_A)];
   gemv_a_body<XT, MX>(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), (int)blockIdx.x - g.wg_a);
 }
 
 template <typename XT, bool MX>
 __global__ __launch_bounds__(kWG) void k_gemv_b_grp(const GroupEntry* __restrict__ e, int count, int par) {
-  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, 1)];
+  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, LN_B)];
   gemv_b_body<XT, MX>(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm, (int)blockIdx.x - g.wg_b);
 }
 
 __global__ __launch_bounds__(kWG) void k_block_grp(const GroupEntry* __restrict__ e, int count, int par) {
-  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, 2)];
+  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, LN_C)];
   block_body(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm, (int)blockIdx.x - g.wg_c);
 }
 
 __global__ __launch_bounds__(kWG) void k_band_grp(const GroupEntry* __restrict__ e, int par) {
   const GroupEntry& g = e[blockIdx.x];
-  if (!g.band) {
+  if (g.band != BAND_FACTOR) {
     if (threadIdx.x == 0) g.B.st[par ^ 1] = g.B.st[par];
     return;
   }
   band_body(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm);
+}
+
+template <int WHICH>
+__global__ __launch_bounds__(kNT, 2) void k_nest(NestView v, const State* __restrict__ sin, State* __restrict__ sout,
+                                                 const Params* __restrict__ prmp) {
+  nest_body<WHICH>(v, sin, sout, prmp, (int)blockIdx.x);
+}
+
+template <int WHICH>
+__global__ __launch_bounds__(kNT, 2) void k_nest_grp(const GroupEntry* __restrict__ e, int count, int par) {
+  const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, WHICH)];
+  if (g.band != BAND_NEST) {
+    if (threadIdx.x == 0) g.B.st[par ^ 1] = g.B.st[par];
+    return;
+  }
+  const NestView v = nest_view(g.D, g.B);
+  nest_body<WHICH>(v, g.B.st + par, g.B.st + (par ^ 1), g.B.prm, (int)blockIdx.x - g.wg_k);
+}
+
+__global__ __launch_bounds__(kWG) void k_nest_finish_grp(const GroupEntry* __restrict__ e, int par) {
+  const GroupEntry& g = e[blockIdx.x];
+  if (g.band != BAND_NEST) {
+    if (threadIdx.x == 0) g.B.st[par ^ 1] = g.B.st[par];
+    return;
+  }
+  nest_finish(g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm);
 }
 
 // State of every problem of a batch after a graph launch (slot 0 of each).
@@ -1106,11 +1231,16 @@ __global__ __launch_bounds__(kWG) void k_gather_states(const GroupEntry* __restr
 
 template <typename XT, bool MX>
 static hipError_t launch_grouped_t(const GroupEntry* e, int count, int wgs, int par, int which, hipStream_t st) {
+  const dim3 g(wgs);
   switch (which) {
-    case 0: hipLaunchKernelGGL((k_gemv_a_grp<XT, MX>), dim3(wgs), dim3(kWG), 0, st, e, count, par); break;
-    case 1: hipLaunchKernelGGL((k_gemv_b_grp<XT, MX>), dim3(wgs), dim3(kWG), 0, st, e, count, par); break;
-    case 2: hipLaunchKernelGGL(k_block_grp, dim3(wgs), dim3(kWG), 0, st, e, count, par); break;
-    default: hipLaunchKernelGGL(k_band_grp, dim3(count), dim3(kWG), 0, st, e, par); break;
+    case LN_A: hipLaunchKernelGGL((k_gemv_a_grp<XT, MX>), g, dim3(kWG), 0, st, e, count, par); break;
+    case LN_B: hipLaunchKernelGGL((k_gemv_b_grp<XT, MX>), g, dim3(kWG), 0, st, e, count, par); break;
+    case LN_C: hipLaunchKernelGGL(k_block_grp, g, dim3(kWG), 0, st, e, count, par); break;
+    case LN_BAND: hipLaunchKernelGGL(k_band_grp, dim3(count), dim3(kWG), 0, st, e, par); break;
+    case LN_NEST1: hipLaunchKernelGGL(k_nest_grp<LN_NEST1>, g, dim3(kNT), 0, st, e, count, par); break;
+    case LN_NEST2: hipLaunchKernelGGL(k_nest_grp<LN_NEST2>, g, dim3(kNT), 0, st, e, count, par); break;
+    case LN_NEST3: hipLaunchKernelGGL(k_nest_grp<LN_NEST3>, g, dim3(kNT), 0, st, e, count, par); break;
+    default: hipLaunchKernelGGL(k_nest_finish_grp, dim3(count), dim3(kWG), 0, st, e, par); break;
   }
   return hipGetLastError();
 }
@@ -1133,34 +1263,49 @@ hipError_t launch_gather_states(const GroupEntry* e, int count, State* out, hipS
 }
 
 template <typename XT, bool MX>
-static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, int par, int which, hipStream_t st) {
+static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, const GroupEntry* self, int par, int which,
+                                    hipStream_t st) {
   const State* sin = B.st + par;
   State* sout = B.st + (par ^ 1);
   switch (which) {
-    case 0:
+    case LN_A:
       hipLaunchKernelGGL((k_gemv_a<XT, MX>), dim3(D.cb1 * D.rb1), dim3(kWG), 0, st, D, B, sin, sout);
       break;
-    case 1:
+    case LN_B:
       hipLaunchKernelGGL((k_gemv_b<XT, MX>), dim3(D.gridB), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
       break;
-    case 3:
+    case LN_C:
+      hipLaunchKernelGGL(k_block, dim3(D.nblk), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
+      break;
+    case LN_BAND:
       hipLaunchKernelGGL(k_band, dim3(1), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
       break;
+    case LN_NEST1:
+      hipLaunchKernelGGL(k_nest<LN_NEST1>, dim3(B.nest.wgs), dim3(kNT), 0, st, nest_view(D, B), sin, sout, B.prm);
+      break;
+    case LN_NEST2:
+      hipLaunchKernelGGL(k_nest<LN_NEST2>, dim3(B.nest.wgs), dim3(kNT), 0, st, nest_view(D, B), sin, sout, B.prm);
+      break;
+    case LN_NEST3:
+      hipLaunchKernelGGL(k_nest<LN_NEST3>, dim3(B.nest.wgs), dim3(kNT), 0, st, nest_view(D, B), sin, sout, B.prm);
+      break;
     default:
-      hipLaunchKernelGGL(k_block, dim3(D.nblk), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
+      hipLaunchKernelGGL(k_nest_finish_grp, dim3(1), dim3(kWG), 0, st, self, par);
       break;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_rotation(const Dims& D, const Bufs& B, int par, int which, hipStream_t st, bool mixed) {
+// self: the problem's own entry in device memory (the K1..K4 launches).
+hipError_t launch_rotation(const Dims& D, const Bufs& B, const GroupEntry* self, int par, int which, hipStream_t st,
+                           bool mixed) {
   switch (D.dtype) {
-    case 0: return mixed ? launch_rotation_t<double, true>(D, B, par, which, st)
-                         : launch_rotation_t<double, false>(D, B, par, which, st);
-    case 1: return mixed ? launch_rotation_t<float, true>(D, B, par, which, st)
-                         : launch_rotation_t<float, false>(D, B, par, which, st);
-    default: return mixed ? launch_rotation_t<uint16_t, true>(D, B, par, which, st)
-                          : launch_rotation_t<uint16_t, false>(D, B, par, which, st);
+    case 0: return mixed ? launch_rotation_t<double, true>(D, B, self, par, which, st)
+                         : launch_rotation_t<double, false>(D, B, self, par, which, st);
+    case 1: return mixed ? launch_rotation_t<float, true>(D, B, self, par, which, st)
+                         : launch_rotation_t<float, false>(D, B, self, par, which, st);
+    default: return mixed ? launch_rotation_t<uint16_t, true>(D, B, self, par, which, st)
+                          : launch_rotation_t<uint16_t, false>(D, B, self, par, which, st);
   }
 }
 
