@@ -276,8 +276,8 @@ flr_status flr_profile_grid(flr_problem h, int32_t B, int32_t reps, double* avg_
 
 /* Profiling of Algorithm 1 (section 3.1): at the handle's current iterate,
  * run `reps` times each (a) the reweighting and assembly of Q = X^T X +
- * lambda1 A + lambda2 B, (b) the blocked Cholesky factor Q = L L^T and (c) the
- * forward and backward triangular solves, on the problem's stream, and report
+ * lambda1 A + lambda2 B, (b) the blocked Cholesky factor Q = L L^T with the
+ * forward solve L z = c and (c) the backward solve, on the problem's stream, and report
  * their average durations in microseconds (HIP events; avg_us: host, 3
  * entries).  Needs a completed FLR_METHOD_CHOLESKY solve on the handle (its
  * dense workspace); the iterate and the last result are left intact.

@@ -10,8 +10,9 @@
 //   factor    blocked right-looking Cholesky, blocks of 64: a panel launch
 //             (every workgroup factors the diagonal block in LDS and solves
 //             its own 64 rows of the panel against it) and an MFMA update of
-//             the trailing lower triangle, tile by tile
-//   solve     L z = c, then L^T b = z, blocked by 64 in one workgroup
+//             the trailing lower triangle, tile by tile; the right-hand side
+//             is one more row of the matrix, so L y = c comes with it
+//   solve     L^T b = y, blocked by 64 in one workgroup
 //   objective f(b) in FP64: 1/2 ||y - X b||^2 (one pass over X) + penalties
 // The host drives the MM loop: one MM step's launches are captured once per
 // solve as a HIP graph and replayed every iteration, with one
@@ -32,7 +33,7 @@
 namespace flr {
 
 constexpr int kNB = 64;                 // Cholesky block
-constexpr int64_t kDenseMaxP = 8192;    // Algorithm 1 keeps two nd x nd FP64 matrices
+constexpr int64_t kDenseMaxP = 8192;    // Algorithm 1 keeps two nd x nd FP64 matrices (and nd entries in LDS)
 
 typedef double dx4v __attribute__((ext_vector_type(4)));
 
@@ -84,10 +85,13 @@ __global__ __launch_bounds__(kWG) void k_dense_assemble(int64_t p, int64_t nd, c
 // 16 s .. 16 s + 15, in registers.  At column c the owning wave publishes the
 // column of every block it holds in LDS (double-buffered by step parity: one
 // barrier per column) and every wave applies the rank-1 update to its own
-// columns.  Workgroup 0 writes the factored diagonal block to `diag` (others
+// columns; the columns are divided by their pivots' roots at the end, off that
+// chain.  The last row block is R, 64
+// rows of which the first holds the right-hand side: it comes out as y^T, the
+// forward solve L y = c.  Workgroup 0 writes the factored diagonal block to `diag` (others
 // may still be reading it from Q; the update launch moves it into Q); every
 // workgroup writes its own row blocks of L back into Q.  Q column-major, ld
-// nd; nrb = row blocks in the panel, the diagonal one included; *bad set on a
+// nd; nrb = row blocks of Q in the panel, the diagonal one included; *bad set on a
 // pivot that is not positive and finite.
 // Panel row blocks per workgroup besides the diagonal block.  One is the
 // fastest measured (order 512: factorization 275 us against 310 us with two
@@ -95,17 +99,21 @@ __global__ __launch_bounds__(kWG) void k_dense_assemble(int64_t p, int64_t nd, c
 constexpr int kPR = 1;
 
 __global__ __launch_bounds__(kWG) void k_chol_panel(double* __restrict__ Q, int64_t nd, int64_t kb, int nrb,
-                                                    int* bad, double* __restrict__ diag) {
+                                                    int* bad, double* __restrict__ diag, double* __restrict__ R) {
   __shared__ __align__(16) double cbuf[2][(1 + kPR) * kNB];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int first = 1 + kPR * (int)blockIdx.x;          // first row block beyond the diagonal one
-  const int nset = 1 + min(kPR, max(0, nrb - first));   // row sets held, the diagonal block included
-  double v[1 + kPR][16];
+  const int nset = 1 + min(kPR, max(0, nrb + 1 - first));  // row sets held, the diagonal block included
+  // held row set m, panel column c
+  auto at = [&](int m, int c) -> double* {
+    const int block = m == 0 ? 0 : first + m - 1;
+    return block < nrb ? Q + (kb + c) * nd + kb + (int64_t)block * kNB + lane : R + (kb + c) * kNB + lane;
+  };
+  double v[1 + kPR][16], pv[16];
 #pragma unroll
   for (int m = 0; m <= kPR; ++m) {
-    const int64_t row = kb + (m == 0 ? 0 : (int64_t)(first + m - 1) * kNB) + lane;
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) v[m][kk] = m < nset ? Q[(kb + 16 * wave + kk) * nd + row] : 0.0;
+    for (int kk = 0; kk < 16; ++kk) v[m][kk] = m < nset ? *at(m, 16 * wave + kk) : 0.0;
   }
   bool ok = true;
 #pragma unroll
@@ -139,16 +147,21 @@ __global__ __launch_bounds__(kWG) void k_chol_panel(double* __restrict__ Q, int6
 #pragma unroll
           for (int m = 0; m <= kPR; ++m) v[m][kk] = fma(-q[m], lc, v[m][kk]);
         }
-        const double d = sqrt(piv), rd = 1.0 / d;
-        v[0][k] = lane == c ? d : lane > c ? col[lane] * rd : 0.0;
-#pragma unroll
-        for (int m = 1; m <= kPR; ++m) v[m][k] = col[m * kNB + lane] * rd;
+        pv[k] = piv;  // v[.][k] stays the unscaled column until the end
       }
     }
   }
   if (!ok) {  // the same decision in every thread
     if (tid == 0 && blockIdx.x == 0) *bad = 1;
     return;
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int c = 16 * wave + k;
+    const double d = sqrt(pv[k]), rd = 1.0 / d;
+    v[0][k] = lane == c ? d : lane > c ? v[0][k] * rd : 0.0;
+#pragma unroll
+    for (int m = 1; m <= kPR; ++m) v[m][k] *= rd;
   }
   if (blockIdx.x == 0) {
 #pragma unroll
@@ -157,9 +170,8 @@ __global__ __launch_bounds__(kWG) void k_chol_panel(double* __restrict__ Q, int6
 #pragma unroll
   for (int m = 1; m <= kPR; ++m) {
     if (m < nset) {
-      const int64_t row = kb + (int64_t)(first + m - 1) * kNB + lane;
 #pragma unroll
-      for (int kk = 0; kk < 16; ++kk) Q[(kb + 16 * wave + kk) * nd + row] = v[m][kk];
+      for (int kk = 0; kk < 16; ++kk) *at(m, 16 * wave + kk) = v[m][kk];
     }
   }
 }
@@ -179,29 +191,34 @@ __global__ __launch_bounds__(kWG) void k_chol_put_diag(double* __restrict__ Q, i
 
 // Trailing update after panel kb (workgroup 0 also moves the factored
 // diagonal block into Q): tile (bi, bj), bi >= bj, of the lower triangle
-// below and right of the panel: C -= L_i L_j^T with K = 64 (the panel
+// below and right of the panel, or (the last nt workgroups) tile bj of R, the
+// row block of the right-hand side: C -= L_i L_j^T with K = 64 (the panel
 // columns), on v_mfma_f64_16x16x4f64 (same lane assignment as the grid
 // products: A rows fed in the order 4 (i % 4) + i / 4, so each lane holds four
 // consecutive rows of one output column).
 __global__ __launch_bounds__(kWG) void k_chol_update(double* __restrict__ Q, int64_t nd, int64_t kb, int nt,
-                                                     const double* __restrict__ diag) {
+                                                     const double* __restrict__ diag, double* __restrict__ R) {
   constexpr int LDK = kNB + 4;
   if (blockIdx.x == 0) put_diag(Q, nd, kb, diag);  // disjoint from every tile read or written below
   __shared__ __align__(16) double As[kNB * LDK];
   __shared__ __align__(16) double Bs[kNB * LDK];
   // tile index -> (bi, bj) with bi >= bj over nt blocks
-  int t = blockIdx.x, bj = 0;
-  while (t >= nt - bj) {
+  const bool rhs = (int)blockIdx.x >= nt * (nt + 1) / 2;
+  int t = rhs ? 0 : blockIdx.x, bj = rhs ? (int)blockIdx.x - nt * (nt + 1) / 2 : 0;
+  while (!rhs && t >= nt - bj) {
     t -= nt - bj;
     ++bj;
   }
   const int bi = bj + t;
   const int64_t base = kb + kNB;
-  const int64_t i0 = base + (int64_t)bi * kNB, j0 = base + (int64_t)bj * kNB;
+  const int64_t j0 = base + (int64_t)bj * kNB;
+  // row block i: its first row and leading dimension
+  double* Qi = rhs ? R : Q + base + (int64_t)bi * kNB;
+  const int64_t ldi = rhs ? kNB : nd;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int e = tid; e < kNB * kNB; e += kWG) {
     const int m = e % kNB, k = e / kNB;  // coalesced along m
-    As[m * LDK + k] = Q[(kb + k) * nd + i0 + m];
+    As[m * LDK + k] = Qi[(kb + k) * ldi + m];
     Bs[m * LDK + k] = Q[(kb + k) * nd + j0 + m];
   }
   __syncthreads();
@@ -234,8 +251,8 @@ __global__ __launch_bounds__(kWG) void k_chol_update(double* __restrict__ Q, int
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const int64_t n = j0 + wn * 32 + b * 16 + i16;
-      const int64_t m = i0 + wm * 32 + a * 16 + g4;
-      dx4v* dst = reinterpret_cast<dx4v*>(Q + n * nd + m);
+      const int64_t m = wm * 32 + a * 16 + g4;
+      dx4v* dst = reinterpret_cast<dx4v*>(Qi + n * ldi + m);
       *dst = *dst - acc[a][b];
     }
 }
@@ -248,87 +265,75 @@ __device__ inline double lane_value(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Triangular solves with the factor (one workgroup): forward L z = rhs, then
-// backward L^T out = z, both blocked by 64 and right-looking.  Per block one
-// wave substitutes through the diagonal block (staged in LDS with the
-// reciprocals of its diagonal; the solved value passed between lanes by
-// readlane) while the other three waves stage the next diagonal block into
-// the second LDS buffer; then all 256 threads subtract the solved block from
-// every row still to come - forward, row i reads L[i][block] (64 coalesced
-// loads); backward, row j reads L[block][j], 64 consecutive entries of column
-// j - so each block costs one round of loads instead of one per earlier block.
-__global__ __launch_bounds__(kWG) void k_chol_solve(const double* __restrict__ Q, int64_t nd, int64_t p,
-                                                    const double* __restrict__ rhs, double* __restrict__ z,
-                                                    double* __restrict__ out) {
-  constexpr int LD = kNB + 1;
+// Backward solve L^T x = y with the factor (one workgroup of 16 waves; y is the
+// first row of R).  Block b, columns c of 64: x_c = (y_c - sum_{r > c} L_rc x_r)
+// / L_cc.  Wave 0 substitutes through the diagonal block (staged in LDS, the
+// solved value passed by readlane) while the other waves sum the next block's
+// columns over every row solved so far, lanes along a column (coalesced); the 64
+// rows that wave 0 is solving follow with loads issued before.  The serial
+// substitution bounds it.  With the forward solve in the factor (2 us more per
+// panel launch): 394 -> 113 us at order 1024.
+constexpr int kSolveT = 1024;
+
+__global__ __launch_bounds__(kSolveT) void k_chol_back(const double* __restrict__ Q, int64_t nd,
+                                                       const double* __restrict__ R, double* __restrict__ out) {
+  constexpr int LD = kNB + 1, NW = kSolveT / 64 - 1, NC = (kNB + NW - 1) / NW;
+  __shared__ double xs[kDenseMaxP];
   __shared__ double Lb[2][kNB * LD];  // Lb[.][c * LD + r] = L[b*64 + r][b*64 + c]
   __shared__ double rdg[2][kNB];      // 1 / L[b*64 + r][b*64 + r]
-  __shared__ double zb[kNB];          // the block just solved
+  __shared__ double tb[kNB];          // right-hand side of the block to substitute
   const int tid = threadIdx.x, r = tid & 63, wave = tid >> 6;
   const int nb = (int)(nd / kNB);
-  // diagonal block b into buffer u by the threads first .. kWG - 1
-  auto stage = [&](int b, int u, int first) {
+  auto stage = [&](int b, int first) {  // diagonal block b by the threads first ..
     const int64_t o = (int64_t)b * kNB;
-    for (int e = tid - first; e < kNB * kNB; e += kWG - first) {
+    const int u = b & 1;
+    for (int e = tid - first; e < kNB * kNB; e += kSolveT - first) {
       const int c = e >> 6, rr = e & 63;
       Lb[u][c * LD + rr] = Q[(o + c) * nd + o + rr];
     }
-    if (tid - first < kNB && tid >= first) rdg[u][tid - first] = 1.0 / Q[(o + tid - first) * nd + o + tid - first];
+    if (tid >= first && tid - first < kNB)
+      rdg[u][tid - first] = 1.0 / Q[(o + tid - first) * nd + o + tid - first];
   };
-  for (int64_t i = tid; i < nd; i += kWG) z[i] = i < p ? rhs[i] : 0.0;
-  stage(0, 0, 0);
-  __syncthreads();
-  // forward: z holds the running right-hand side; block b is final once blocks < b are applied
-  for (int b = 0; b < nb; ++b) {
-    const int u = b & 1;
-    if (wave == 0) {
-      const int64_t i = (int64_t)b * kNB + r;
-      double t = z[i];
-      for (int c = 0; c < kNB; ++c) {
-        const double zc = lane_value(t, c) * rdg[u][c];
-        if (r == c) t = zc;
-        else if (r > c) t = fma(-Lb[u][c * LD + r], zc, t);
-      }
-      z[i] = t;
-      zb[r] = t;
-    } else if (b + 1 < nb) {
-      stage(b + 1, u ^ 1, 64);
-    }
-    __syncthreads();
-    const double* Lc = Q + (int64_t)b * kNB * nd;  // column b*64 of L
-    for (int64_t i = (int64_t)(b + 1) * kNB + tid; i < nd; i += kWG) {
-      double s = 0.0;
-#pragma unroll 16
-      for (int c = 0; c < kNB; ++c) s = fma(Lc[(int64_t)c * nd + i], zb[c], s);
-      z[i] -= s;
-    }
-    __syncthreads();
-  }
-  // backward: z now holds the running right-hand side of L^T out = z
-  stage(nb - 1, (nb - 1) & 1, 0);
+  stage(nb - 1, 0);
+  if (tid < kNB) tb[tid] = R[((int64_t)(nb - 1) * kNB + tid) * kNB];
   __syncthreads();
   for (int b = nb - 1; b >= 0; --b) {
-    const int u = b & 1;
+    const int64_t o = (int64_t)b * kNB, on = o - kNB;
+    double acc[NC], near[NC];
     if (wave == 0) {
-      const int64_t i = (int64_t)b * kNB + r;  // column of L
-      double t = z[i];
+      const double* L = Lb[b & 1];
+      double t = tb[r];
+#pragma unroll 8
       for (int c = kNB - 1; c >= 0; --c) {
-        const double xc = lane_value(t, c) * rdg[u][c];
-        if (r == c) t = xc;
-        else if (r < c) t = fma(-Lb[u][r * LD + c], xc, t);
+        const double xc = lane_value(t, c) * rdg[b & 1][c];
+        const double lrc = L[r * LD + c];
+        t = r == c ? xc : r < c ? fma(-lrc, xc, t) : t;
       }
-      out[i] = t;
-      zb[r] = t;
+      out[o + r] = t;
+      xs[o + r] = t;
     } else if (b > 0) {
-      stage(b - 1, u ^ 1, 64);
+      stage(b - 1, 64);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int c = wave - 1 + q * NW;
+        acc[q] = 0.0;
+        near[q] = 0.0;
+        if (c < kNB) {
+          const double* col = Q + (on + c) * nd;
+          near[q] = col[o + r];
+#pragma unroll 4
+          for (int64_t i = o + kNB + r; i < nd; i += 64) acc[q] = fma(col[i], xs[i], acc[q]);
+        }
+      }
     }
     __syncthreads();
-    for (int64_t j = tid; j < (int64_t)b * kNB; j += kWG) {
-      const double* qc = Q + j * nd + (int64_t)b * kNB;  // L[b*64 .. b*64+63][j]
-      double s = 0.0;
-#pragma unroll 16
-      for (int c = 0; c < kNB; ++c) s = fma(qc[c], zb[c], s);
-      z[j] -= s;
+    if (b > 0 && wave > 0) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int c = wave - 1 + q * NW;
+        const double s = wave_sum(fma(near[q], xs[o + r], acc[q]));
+        if (c < kNB && r == 0) tb[c] = R[(on + c) * kNB] - s;
+      }
     }
     __syncthreads();
   }
@@ -357,9 +362,14 @@ __global__ __launch_bounds__(kWG) void k_dense_rowres(const XT* __restrict__ X, 
   }
 }
 
-// The pivot flag cleared by a kernel (graphs here record no memset nodes).
-__global__ __launch_bounds__(kWG) void k_clear_flag(int* __restrict__ flag) {
-  if (threadIdx.x == 0) *flag = 0;
+// Start of a factorization: the right-hand side into row 0 of R (zero rows
+// below it, zero past p) and the pivot flag cleared (graphs here record no
+// memset nodes).
+__global__ __launch_bounds__(kWG) void k_dense_rhs(int64_t p, int64_t nd, const double* __restrict__ c,
+                                                   double* __restrict__ R, int* __restrict__ flag) {
+  const int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x;
+  if (e == 0) *flag = 0;
+  if (e < nd * kNB) R[e] = e % kNB == 0 && e / kNB < p ? c[e / kNB] : 0.0;
 }
 
 // G[j][j] = 1 for j < p (the Gram matrix of X = I; the rest stays zero).
@@ -431,7 +441,7 @@ struct DenseWork {
   double* Q = nullptr;    // the system, then its Cholesky factor
   double* a = nullptr;
   double* w = nullptr;
-  double* z = nullptr;
+  double* R = nullptr;    // 64 x nd column-major: row 0 the right-hand side, then y of L y = c
   double* xn = nullptr;   // solution of the current MM step
   double* rr = nullptr;   // n row residuals
   double* pen = nullptr;  // p row penalties
@@ -445,7 +455,7 @@ struct DenseWork {
 void dense_free(flr_problem h) {
   DenseWork* dw = h->dense;
   if (!dw) return;
-  for (void* p : {(void*)dw->G, (void*)dw->Q, (void*)dw->a, (void*)dw->w, (void*)dw->z, (void*)dw->xn, (void*)dw->rr,
+  for (void* p : {(void*)dw->G, (void*)dw->Q, (void*)dw->a, (void*)dw->w, (void*)dw->R, (void*)dw->xn, (void*)dw->rr,
                   (void*)dw->pen, (void*)dw->scal, (void*)dw->diag, (void*)dw->bad})
     if (p) (void)hipFree(p);
   if (dw->h_out) (void)hipHostFree(dw->h_out);
@@ -503,7 +513,7 @@ static flr_status dense_prepare_once(flr_problem h) {
   DCK(al(&dw->Q, nd2, sizeof(double)));
   DCK(al(&dw->a, (size_t)D.p, sizeof(double)));
   DCK(al(&dw->w, (size_t)std::max<int64_t>(h->nnz, 1), sizeof(double)));
-  DCK(al(&dw->z, (size_t)dw->nd, sizeof(double)));
+  DCK(al(&dw->R, (size_t)dw->nd * kNB, sizeof(double)));
   DCK(al(&dw->xn, (size_t)std::max<int64_t>(dw->nd, D.p_pad), sizeof(double)));  // the solve writes nd entries
   DCK(al(&dw->rr, (size_t)D.n, sizeof(double)));
   DCK(al(&dw->pen, (size_t)D.p, sizeof(double)));
@@ -562,18 +572,22 @@ static hipError_t dense_objective(flr_problem h, const double* b, double l1, dou
   return hipGetLastError();
 }
 
-// Q = L L^T in place (lower triangle); *bad set on a failed pivot.
+// Q = L L^T in place (lower triangle) and L y = c (row 0 of R); *bad set on a
+// failed pivot.
 static hipError_t dense_factor(flr_problem h) {
   DenseWork* dw = h->dense;
   const int64_t nd = dw->nd;
+  hipLaunchKernelGGL(k_dense_rhs, dim3((unsigned)((nd * kNB + kWG - 1) / kWG)), dim3(kWG), 0, h->stream, h->D.p, nd,
+                     h->B.c, dw->R, dw->bad);
   for (int64_t kb = 0; kb < nd; kb += kNB) {
     const int nrb = (int)((nd - kb) / kNB);
-    const unsigned groups = (unsigned)std::max(1, (nrb - 1 + kPR - 1) / kPR);
-    hipLaunchKernelGGL(k_chol_panel, dim3(groups), dim3(kWG), 0, h->stream, dw->Q, nd, kb, nrb, dw->bad, dw->diag);
+    const unsigned groups = (unsigned)((nrb + kPR - 1) / kPR);  // the row blocks below the diagonal one, and R
+    hipLaunchKernelGGL(k_chol_panel, dim3(groups), dim3(kWG), 0, h->stream, dw->Q, nd, kb, nrb, dw->bad, dw->diag,
+                       dw->R);
     const int nt = nrb - 1;
     if (nt > 0)
-      hipLaunchKernelGGL(k_chol_update, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(kWG), 0, h->stream, dw->Q, nd, kb,
-                         nt, dw->diag);
+      hipLaunchKernelGGL(k_chol_update, dim3((unsigned)(nt * (nt + 1) / 2 + nt)), dim3(kWG), 0, h->stream, dw->Q, nd,
+                         kb, nt, dw->diag, dw->R);
     else
       hipLaunchKernelGGL(k_chol_put_diag, dim3(1), dim3(kWG), 0, h->stream, dw->Q, nd, kb, dw->diag);
     const hipError_t e = hipGetLastError();
@@ -594,11 +608,10 @@ static hipError_t dense_step(flr_problem h, double l1, double l2, double eps) {
                      dw->a, dw->w);
   hipLaunchKernelGGL(k_dense_assemble, dim3((unsigned)dw->nd), dim3(kWG), 0, h->stream, D.p, dw->nd, dw->G, dw->Q,
                      dw->a, dw->w, h->B.rowptr, h->B.col, l1, l2);
-  hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(kWG), 0, h->stream, dw->bad);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = dense_factor(h)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_chol_solve, dim3(1), dim3(kWG), 0, h->stream, dw->Q, dw->nd, D.p, h->B.c, dw->z, dw->xn);
+  hipLaunchKernelGGL(k_chol_back, dim3(1), dim3(kSolveT), 0, h->stream, dw->Q, dw->nd, dw->R, dw->xn);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = dense_objective(h, dw->xn, l1, l2)) != hipSuccess) return e;
   if ((e = hipMemcpyAsync(&dw->h_out->f, dw->scal, sizeof(double), hipMemcpyDeviceToHost, h->stream)) != hipSuccess)
@@ -715,8 +728,8 @@ flr_status dense_run(flr_problem h, double l1, double l2, double tol, const flr_
 
 // Average durations (us, HIP events on the problem's stream) of the three
 // stages of one Algorithm 1 step at the current iterate: reweighting plus
-// assembly of Q, the blocked Cholesky factor, and the two triangular solves.
-// Writes only Q, a, w, z and xn; the iterate and the last result stay intact.
+// assembly of Q, the blocked Cholesky factor with the forward solve, and the
+// backward solve.  Writes only Q, R, a, w and xn; the iterate and the last result stay intact.
 flr_status dense_profile(flr_problem h, double l1, double l2, int32_t reps, double* avg_us) {
   const Dims& D = h->D;
   DenseWork* dw = h->dense;
@@ -746,7 +759,7 @@ flr_status dense_profile(flr_problem h, double l1, double l2, int32_t reps, doub
         ms[1] += t;
       }
       if (stage == 2) {
-        hipLaunchKernelGGL(k_chol_solve, dim3(1), dim3(kWG), 0, h->stream, dw->Q, dw->nd, D.p, h->B.c, dw->z, dw->xn);
+        hipLaunchKernelGGL(k_chol_back, dim3(1), dim3(kSolveT), 0, h->stream, dw->Q, dw->nd, dw->R, dw->xn);
         DCK(hipGetLastError());
       }
     }
