@@ -7,8 +7,11 @@
 // the factor is computed once per MM iteration and every PCG step applies it
 // with two triangular sweeps.
 //
-// Layouts (W = bw + 1 entries per row / column), stored as the sweeps use
-// them, i.e. divided by the diagonal of the step that applies them:
+// Two forms, by W = bw + 1 (band_blocks): blocks of NB rows whose diagonal
+// blocks of L are inverted (16 <= W <= 107, below), and for the other widths a
+// chain of single rows.  Layouts of the latter (W entries per row / column),
+// stored as the sweeps use them, i.e. divided by the diagonal of the step that
+// applies them:
 //   Lb  column-major band, Lb[j*W + k]  = L_{j+k, j} / L_jj  (column j; k >= 1)
 //   LbT row-major band,    LbT[i*W + k] = L_{i, i-k} / L_ii  (row i; k >= 1)
 //   Lb[j*W] = LbT[j*W] = L_jj, invd[j] = 1 / L_jj
@@ -33,6 +36,15 @@ namespace flr {
 constexpr int kBandLds = 13312;   // doubles of LDS the band routines use (104 KiB)
 constexpr int kBandMaxW = 1025;   // widest band the sweeps handle (NR = 17 ring registers)
 constexpr int kPanelMaxW = 107;   // widest band the register-panel factorization takes (its LDS window)
+
+// Rows per block of the blocked sweeps, 0 for the row-by-row ones.  NB <= W, so
+// that a block's inverse fits into the unused corner of its band.  Narrower
+// bands have too little work per block for its two barriers (at NB = 8 no better
+// than the 50 ns per row of the chain); wider ones are factored in place
+// in global memory (band_factor_blocked), which needs the plain layout.
+__host__ __device__ inline int band_blocks(int W) {
+  return W > kPanelMaxW || W < 16 ? 0 : W < 32 ? 16 : W < 64 ? 32 : 64;
+}
 
 // Ring registers per lane: 64*NR slots must hold the bw elements ahead of the
 // current one plus the 64 of the chunk being consumed.
@@ -164,9 +176,12 @@ __device__ inline bool band_factor_blocked(double* __restrict__ Lb, double* __re
 // trip per NB pivots instead of one per pivot, with two barriers per panel.
 // 256 threads; false in every thread on a pivot that is not positive and
 // finite.
-template <int NB>
-__device__ inline bool band_factor_panels(double* __restrict__ Lb, double* __restrict__ LbT,
-                                          double* __restrict__ invd, int64_t p, int W, double* __restrict__ lds) {
+// BR > 0: L goes out in the layout of the blocked sweeps with blocks of BR rows
+// (LbT the forward blocks, Lb - in place of the assembled band, whose columns of
+// the block being written are all in the window by then - the backward ones).
+template <int NB, int BR>
+__device__ inline bool band_factor_panels(double* Lb, double* __restrict__ LbT, double* __restrict__ invd, int64_t p,
+                                          int W, double* __restrict__ lds) {
   constexpr int LP = NB + 1;                   // Lp row stride, odd: 16 consecutive rows in distinct banks
   constexpr int NXT = (NB * kPanelMaxW + 63) / 64;  // entering band entries per lane of wave 0
   constexpr int kTB = 7;                       // 16-wide blocks of the trailing triangle (W - 1 <= 112)
@@ -278,12 +293,38 @@ __device__ inline bool band_factor_panels(double* __restrict__ Lb, double* __res
       // the panel's columns of L: Lb scaled by 1/L_jj below the diagonal,
       // LbT unscaled (the caller scales its rows), invd
       const int k = tid - 64;
-      for (int jj = 0; jj < w; ++jj) {
-        const int64_t j = j0 + jj;
-        if (k < W && j + k < p) {
-          const double v = Lp[(jj + k) * LP + jj];
-          Lb[j * W + k] = k ? v * sh_inv[jj] : v;
-          LbT[(j + k) * W + k] = v;
+      if constexpr (BR > 0) {
+        // a thread per row i = j0 + k: eight neighbouring entries of the backward
+        // block, and of the forward blocks lanes along the rows
+        const int64_t i = j0 + k;
+        if (k < R && i < p) {
+          const int64_t bi = i / BR, bj = j0 / BR;  // the panel lies in one block (NB divides BR)
+          const int ri = (int)(i - bi * BR), cj = (int)(j0 - bj * BR);
+          const int ld = p - bi * BR < BR ? (int)(p - bi * BR) : BR;
+          double* f = LbT + bi * BR * W + ri;
+          if (bi == bj) {
+            for (int jj = 0; jj < w; ++jj)
+              if (k >= jj) f[(int64_t)(cj + jj ? cj + jj - 1 : W - 1) * ld] = Lp[k * LP + jj];
+          } else {
+            const int kk = (int)(j0 - bi * BR) + W - 1;
+            double* g = Lb + bj * BR * W + (int64_t)(W - 2 - (int)(i - (bj + 1) * BR)) * BR + (BR - 1 - cj);
+            for (int jj = 0; jj < w; ++jj) {
+              if (k - jj < W) {
+                const double v = Lp[k * LP + jj];
+                f[(int64_t)(kk + jj) * ld] = v;
+                g[-jj] = v;
+              }
+            }
+          }
+        }
+      } else {
+        for (int jj = 0; jj < w; ++jj) {
+          const int64_t j = j0 + jj;
+          if (k < W && j + k < p) {
+            const double v = Lp[(jj + k) * LP + jj];
+            Lb[j * W + k] = k ? v * sh_inv[jj] : v;
+            LbT[(j + k) * W + k] = v;
+          }
         }
       }
       if (k < w) invd[j0 + k] = sh_inv[k];
@@ -334,18 +375,238 @@ __device__ inline bool band_factor_panels(double* __restrict__ Lb, double* __res
   return true;
 }
 
-// Cholesky factor of the assembled band, in place: the register-panel
-// factorization above when its window fits the band LDS (W <= 107), the
-// blocked one with the trailing update in global memory otherwise.  256
-// threads; returns false in every thread when a pivot is not positive and
-// finite.
-__device__ inline bool band_factor(double* __restrict__ Lb, double* __restrict__ LbT, double* __restrict__ invd,
-                                   int64_t p, int W, double* __restrict__ lds) {
+// ---------------------------------------------------------------------------
+// Blocked sweeps.  A sweep solves L y = r (or, over reversed indexes, L^T z = y)
+// in blocks of NB rows: t = r_b - (band part of L left of the block) y, then y_b
+// = inv(L_bb) t.  In solve order v (v = j forward, p - 1 - j backward) a block
+// that starts at v0 is stored as W columns of its NB rows (the last rows of the
+// index range may form a shorter block; ld is its row count):
+//   column kk < W - 1, rows i <= kk:  the coupling to element v0 - (W - 1) + kk,
+//                      rows i > kk:   column kk + 1 of inv(L_bb),
+//   column W - 1:                     column 0 of inv(L_bb):
+// the corner that the band leaves empty holds the inverse, so the blocks take the
+// band's own p W entries.  Inverting only the triangular diagonal blocks keeps
+// the sweep a backward-stable substitution (L is an M-matrix factor: its entries
+// off the diagonal are <= 0 and those of the inverse come out without
+// cancellation).
+// ---------------------------------------------------------------------------
+
+// inv(L_bb) of every block, in place of L_bb in the forward blocks and into the
+// backward ones.  One wave per block at a time: lane c substitutes column c with
+// L_bb in LDS (packed rows, read as broadcasts), its values in registers.
+template <int NB>
+__device__ inline void band_invert_blocks(double* __restrict__ bwd, double* __restrict__ fwd,
+                                          const double* __restrict__ invd, int64_t p, int W, double* lds) {
+  constexpr int TRI = NB * (NB + 1) / 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double* T = lds + wave * (TRI + NB);  // row r at r (r + 1) / 2, then 1 / L_rr
+  double* D = T + TRI;
+  const int64_t nblk = (p + NB - 1) / NB;
+  for (int64_t b = wave; b < nblk; b += 4) {
+    const int ld = p - b * NB < NB ? (int)(p - b * NB) : NB;
+    double* f = fwd + b * NB * W;
+    double* g = bwd + b * NB * W;
+    for (int c = 0; c < ld; ++c)
+      if (lane < ld && lane >= c) T[lane * (lane + 1) / 2 + c] = f[(int64_t)(c ? c - 1 : W - 1) * ld + lane];
+    if (lane < ld) D[lane] = invd[b * NB + lane];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double x[NB];
+#pragma unroll
+    for (int r = 0; r < NB; ++r) {
+      double s0 = r == lane ? 1.0 : 0.0, s1 = 0.0;
+#pragma unroll
+      for (int k = 0; k < r; ++k) {
+        if (k & 1)
+          s1 = fma(-T[r * (r + 1) / 2 + k], x[k], s1);
+        else
+          s0 = fma(-T[r * (r + 1) / 2 + k], x[k], s0);
+      }
+      x[r] = r < ld ? (s0 + s1) * D[r] : 0.0;
+    }
+    if (lane < ld) {
+#pragma unroll
+      for (int r = 0; r < NB; ++r) {
+        if (r < ld && r >= lane) {  // inv(L_bb)[r][lane]
+          f[(int64_t)(lane ? lane - 1 : W - 1) * ld + r] = x[r];
+          const int c = ld - 1 - r;  // its column over reversed indexes
+          g[(int64_t)(c ? c - 1 : W - 1) * ld + (ld - 1 - lane)] = x[r];
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  __syncthreads();
+}
+
+// One blocked sweep by 256 threads: thread (i, stream) holds row i of every NS-th
+// column of a block in registers, loaded ahead.  Per block two LDS
+// barriers: after the band part (partial sums of the streams) and after the
+// inverse (likewise); every stream forms t and y itself, and every wave keeps its
+// own copy of the last solution values, twice in a row of 2 H so that a block
+// reads them at fixed offsets.  Measured at W = 101, p = 10^4: two sweeps 0.61 ms
+// for one column (1.09 with the row-by-row chain; 0.35 of it the arithmetic chain,
+// 1.1 us per block, the rest the issue of the loads) and 0.91 ms with 256 columns
+// (1.24; 4.1 GB, 4.5 TB/s: the loads bound it).
+// U >= W / NS columns per stream; the ones past the band repeat column W - 1 and
+// meet a zero.
+template <int NB, int U, int WMIN>
+__device__ __forceinline__ void band_sweep_blocks(const double* __restrict__ r, double* __restrict__ out,
+                                                  const double* __restrict__ Z, int64_t p, int W, bool fwd,
+                                                  double* __restrict__ lds) {
+  constexpr int NS = kWG / NB;     // streams
+  constexpr int UI = NB / NS;      // columns per stream with a part of the inverse
+  constexpr int H = 256;           // history slots
+  static_assert(NS * U + NB <= H && NB % NS == 0 && U >= UI, "history or stream split");
+  const int tid = threadIdx.x, lane = tid & 63, i = tid % NB;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int st = NB == 64 ? wave : tid / NB;
+  double* part = lds;                  // [NS][NB]
+  double* part2 = lds + kWG;           // [NS][NB]
+  double* hist = lds + 2 * kWG + wave * 2 * H;
+  const int nfull = (int)(p / NB), tail = (int)(p - (int64_t)nfull * NB);
+  for (int q = lane; q < 2 * H; q += 64) hist[q] = 0.0;
+  int v0 = 0;  // elements solved
+  // this thread's offset into a full block of its columns that may be past the band
+  int clamped[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int kk = st + NS * u;
+    clamped[u] = (kk < W ? kk : W - 1) * NB + i;
+  }
+  // block b (ld rows) into registers: its columns, column W - 1 and the right-hand side
+  auto load = [&](int b, double (&v)[U], double& vl, double& rv) {
+    const double* z = Z + (int64_t)b * NB * W;
+    const double* zt = z + tid;  // column st, row i
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = NS * u + NS <= WMIN ? zt[NS * NB * u] : z[clamped[u]];
+    vl = z[(W - 1) * NB + i];
+    rv = r[(int64_t)b * NB + (fwd ? i : NB - 1 - i)];
+  };
+  auto load_tail = [&](double (&v)[U], double& vl, double& rv) {
+    const double* z = Z + (int64_t)nfull * NB * W;
+    const int ii = i < tail ? i : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kk = st + NS * u;
+      v[u] = z[(kk < W ? kk : W - 1) * tail + ii];
+    }
+    vl = z[(W - 1) * tail + ii];
+    rv = r[(int64_t)nfull * NB + (fwd ? ii : tail - 1 - ii)];
+  };
+  auto step = [&](int b, int ld, const double (&v)[U], double vl, double rv) {
+    const double* h = hist + ((v0 - (W - 1)) & (H - 1)) + st;  // element v0 - (W - 1) + st
+    double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kk = st + NS * u;
+      double y = h[NS * u];
+      if (NS * u + NS >= WMIN) y = kk < W - 1 ? y : 0.0;
+      if (u < UI) y = i > kk ? 0.0 : y;
+      if (u & 1)
+        a1 = fma(v[u], y, a1);
+      else
+        a0 = fma(v[u], y, a0);
+    }
+    part[st * NB + i] = a0 + a1;
+    lds_barrier();
+    double t = i < ld ? rv : 0.0;
+#pragma unroll
+    for (int q = 0; q < NS; ++q) t -= part[q * NB + i];
+    if (i >= ld) t = 0.0;
+    double c0 = st == 0 ? vl * (NB == 64 ? readlane_f64(t, 0) : __shfl(t, lane & ~(NB - 1), 64)) : 0.0, c1 = 0.0;
+#pragma unroll
+    for (int u = 0; u < UI; ++u) {
+      const int kk = st + NS * u;
+      const int c = kk + 1 < NB ? kk + 1 : 0;  // kk = NB - 1 holds no column of the inverse
+      double tc = NB == 64 ? readlane_f64(t, c) : __shfl(t, (lane & ~(NB - 1)) + c, 64);
+      tc = i > kk ? tc : 0.0;
+      if (u & 1)
+        c1 = fma(v[u], tc, c1);
+      else
+        c0 = fma(v[u], tc, c0);
+    }
+    part2[st * NB + i] = c0 + c1;
+    lds_barrier();
+    double y = 0.0;
+#pragma unroll
+    for (int q = 0; q < NS; ++q) y += part2[q * NB + i];
+    if (i >= ld) y = 0.0;
+    if (lane < NB) {
+      const int s0 = (v0 + i) & (H - 1);
+      hist[s0] = y;
+      hist[s0 + H] = y;
+    }
+    if (tid < ld) out[(int64_t)b * NB + (fwd ? i : ld - 1 - i)] = y;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    v0 += ld;
+  };
+  double va[U], vb[U], la = 0.0, lb = 0.0, ra = 0.0, rb = 0.0;
+  __syncthreads();
+  if (!fwd && tail) {  // the short block is the first of the backward sweep and the last of the forward one
+    load_tail(va, la, ra);
+    step(nfull, tail, va, la, ra);
+  }
+  // blocks in two register sets, loaded a block ahead (two blocks ahead: the same)
+  auto block = [&](int s) { return fwd ? s : nfull - 1 - s; };
+  if (nfull > 0) load(block(0), va, la, ra);
+  for (int s = 0; s < nfull; s += 2) {
+    if (s + 1 < nfull) load(block(s + 1), vb, lb, rb);
+    step(block(s), NB, va, la, ra);
+    if (s + 1 < nfull) {
+      if (s + 2 < nfull) load(block(s + 2), va, la, ra);
+      step(block(s + 1), NB, vb, lb, rb);
+    }
+  }
+  if (fwd && tail) {
+    load_tail(va, la, ra);
+    step(nfull, tail, va, la, ra);
+  }
+  __syncthreads();
+}
+
+// Both sweeps of the blocked form (fwd, bwd: the blocks; tmp: p doubles).
+template <int NB, int U, int WMIN>
+__device__ __forceinline__ void band_solve_blocks(const double* r, double* tmp, double* z, const double* fwd,
+                                                  const double* bwd, int64_t p, int W, double* lds) {
+  band_sweep_blocks<NB, U, WMIN>(r, tmp, fwd, p, W, true, lds);
+  band_sweep_blocks<NB, U, WMIN>(tmp, z, bwd, p, W, false, lds);
+}
+
+// Cholesky factor of the assembled band: the register-panel factorization above
+// when its window fits the band LDS (W <= 107), the blocked one with the trailing
+// update in global memory otherwise.  256 threads; returns false in every thread
+// when a pivot is not positive and finite.
+__device__ inline bool band_factor(double* Lb, double* __restrict__ LbT, double* __restrict__ invd, int64_t p, int W,
+                                   double* __restrict__ lds) {
   constexpr int NB = 8;
   const int tid = threadIdx.x, nt = blockDim.x;
-  const bool panels = W >= 2 && W <= kPanelMaxW && (int64_t)(NB + W - 1) * (W + NB + 1) <= kBandLds;
-  const bool ok = panels ? band_factor_panels<NB>(Lb, LbT, invd, p, W, lds)
-                         : band_factor_blocked(Lb, LbT, invd, p, W, lds);
+  const int br = band_blocks(W);
+  if (br) {
+    // the forward blocks that reach before the first element: zeros there
+    const int64_t lead = (int64_t)((W - 2) / br + 1) * br;
+    for (int64_t e = tid; e < (lead < p ? lead : p) * W; e += nt) LbT[e] = 0.0;
+    const bool ok = br == 64   ? band_factor_panels<NB, 64>(Lb, LbT, invd, p, W, lds)
+                    : br == 32 ? band_factor_panels<NB, 32>(Lb, LbT, invd, p, W, lds)
+                               : band_factor_panels<NB, 16>(Lb, LbT, invd, p, W, lds);
+    __syncthreads();  // the blocks' entries come from many threads (the panel loop's barriers order LDS only)
+    if (ok) {
+      if (br == 64)
+        band_invert_blocks<64>(Lb, LbT, invd, p, W, lds);
+      else if (br == 32)
+        band_invert_blocks<32>(Lb, LbT, invd, p, W, lds);
+      else
+        band_invert_blocks<16>(Lb, LbT, invd, p, W, lds);
+    }
+    return ok;
+  }
+  const bool ok = W <= kPanelMaxW ? band_factor_panels<NB, 0>(Lb, LbT, invd, p, W, lds)
+                                  : band_factor_blocked(Lb, LbT, invd, p, W, lds);
   // the rescale below reads invd (stored by lane 0) and LbT entries stored
   // by other threads: a full barrier orders those global stores (the panel
   // loop's barriers order LDS only)
@@ -538,6 +799,17 @@ __device__ __forceinline__ void band_solve_nr(const double* r, double* tmp, doub
 // threads; W <= kBandMaxW (checked on the host).  Ends with a barrier.
 __device__ __forceinline__ void band_solve(const double* r, double* tmp, double* z, const double* Lb,
                                            const double* LbT, const double* invd, int64_t p, int W, double* lds) {
+  switch (band_blocks(W)) {
+    case 16: band_solve_blocks<16, 2, 16>(r, tmp, z, LbT, Lb, p, W, lds); return;
+    case 32: band_solve_blocks<32, 8, 32>(r, tmp, z, LbT, Lb, p, W, lds); return;
+    case 64:
+      if (W <= 84)
+        band_solve_blocks<64, 21, 64>(r, tmp, z, LbT, Lb, p, W, lds);
+      else
+        band_solve_blocks<64, 27, 84>(r, tmp, z, LbT, Lb, p, W, lds);
+      return;
+    default: break;
+  }
   switch (band_nr(W)) {
     case 2: band_solve_nr<2>(r, tmp, z, Lb, LbT, invd, p, W, lds); break;
     case 3: band_solve_nr<3>(r, tmp, z, Lb, LbT, invd, p, W, lds); break;

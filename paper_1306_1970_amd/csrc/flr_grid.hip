@@ -192,7 +192,7 @@ __device__ inline double col_apply_m(const GridDev& G, int b, int64_t j, const d
 template <bool BAND>
 __global__ __launch_bounds__(kWG) void k_col(GridDev G, int hold) {
   const int slot = blockIdx.x, tid = threadIdx.x;
-  const int b = G.map[slot];
+  const int b = __builtin_amdgcn_readfirstlane(G.map[slot]);
   __shared__ double lds[24];
   __shared__ double sh2[2 * kWG];
   __shared__ double sh4[4 * kWG];
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kWG) void k_col(GridDev G, int hold) {
   if (s.phase == PH_DONE || (hold && s.phase == PH_END)) return;
   const GridParams prm = *G.prm;
   const bool use_band = BAND && !s.jacobi;
-  const int W = prm.band;
+  const int W = __builtin_amdgcn_readfirstlane(prm.band);
   double* Lbb = BAND ? G.Lb + (int64_t)b * G.p * W : nullptr;
   double* LbTb = BAND ? G.LbT + (int64_t)b * G.p * W : nullptr;
   const double l1 = G.lam1[b], l2 = G.lam2[b];
