@@ -461,20 +461,14 @@ __device__ __forceinline__ void gemv_b_body(const Dims& D, const Bufs& B, const 
       const Mob mb = wg_scan_mob(mob_leaf(dj, ej), sh_s);
       if (tid == kWG - 1) {
         double* o = B.mob + 4 * (int64_t)wg;
-        o[0] = mb.a;
-        o[1] = mb.b;
-        o[2] = mb.c;
-        o[3] = mb.d;
+        put_shared(o, mb.a);
+        put_shared(o + 1, mb.b);
+        put_shared(o + 2, mb.c);
+        put_shared(o + 3, mb.d);
       }
       __shared__ int sh_flag;
       __syncthreads();
-      if (tid == kWG - 1) {  // the thread that wrote publishes
-        __threadfence();
-        const unsigned prev = atomicAdd(B.counter + 16, 1u);
-        const bool last = prev == (unsigned)(K - 1);
-        if (last) __threadfence();
-        sh_flag = last;
-      }
+      if (tid == kWG - 1) sh_flag = arrive(B.counter + 16, K);
       __syncthreads();
       if (sh_flag) {
         // thread t: blocks t e4 .. t e4 + e4 - 1
@@ -486,7 +480,7 @@ __device__ __forceinline__ void gemv_b_body(const Dims& D, const Bufs& B, const 
           const int k = tid * e4 + i;
           const bool in = i < e4 && k < K;
           const double* o = B.mob + 4 * (int64_t)(in ? k : 0);
-          bm[i] = {o[0], o[1], o[2], o[3]};
+          bm[i] = {get_shared(o), get_shared(o + 1), get_shared(o + 2), get_shared(o + 3)};
           if (in) pr = i == 0 ? bm[0] : mob_compose(pr, bm[i]);
         }
         const Mob inc = wg_scan_mob(pr, sh_s);
@@ -534,12 +528,12 @@ __device__ inline void block_local_solve(const Dims& D, const Bufs& B, int b, in
   double sums[4] = {rj * yj, rj * sigj, rj * psij, rj * rj};
   wg_sum4(sums, lds);
   if (tid == 0) {
-    B.blk[BK_B * K + b] = lds2[0];
-    B.blk[BK_YS * K + b] = lds2[1];
-    B.blk[BK_RY * K + b] = sums[0];
-    B.blk[BK_RS * K + b] = sums[1];
-    B.blk[BK_RP * K + b] = sums[2];
-    B.blk[BK_RR * K + b] = sums[3];
+    put_shared(B.blk + BK_B * K + b, lds2[0]);
+    put_shared(B.blk + BK_YS * K + b, lds2[1]);
+    put_shared(B.blk + BK_RY * K + b, sums[0]);
+    put_shared(B.blk + BK_RS * K + b, sums[1]);
+    put_shared(B.blk + BK_RP * K + b, sums[2]);
+    put_shared(B.blk + BK_RR * K + b, sums[3]);
   }
 }
 
@@ -593,15 +587,15 @@ __device__ void combine_blocks_wave(const Dims& D, const Bufs& B, const Params& 
     const int k = k0 + i;
     const bool ok = i < e && k < K;
     const bool okn = i < e && k + 1 < K;
-    fA[i] = ok ? bk[BK_A * K + k] : 1.0;
-    fB[i] = ok ? bk[BK_B * K + k] : 0.0;
-    fRY[i] = ok ? bk[BK_RY * K + k] : 0.0;
-    fRS[i] = ok ? bk[BK_RS * K + k] : 0.0;
-    fRP[i] = ok ? bk[BK_RP * K + k] : 0.0;
-    fRR[i] = ok ? bk[BK_RR * K + k] : 0.0;
-    nPS[i] = okn ? bk[BK_PSIS * K + k + 1] : 0.0;
-    nYS[i] = okn ? bk[BK_YS * K + k + 1] : 0.0;
-    nSS[i] = okn ? bk[BK_SIGS * K + k + 1] : 0.0;
+    fA[i] = ok ? get_shared(bk + BK_A * K + k) : 1.0;
+    fB[i] = ok ? get_shared(bk + BK_B * K + k) : 0.0;
+    fRY[i] = ok ? get_shared(bk + BK_RY * K + k) : 0.0;
+    fRS[i] = ok ? get_shared(bk + BK_RS * K + k) : 0.0;
+    fRP[i] = ok ? get_shared(bk + BK_RP * K + k) : 0.0;
+    fRR[i] = ok ? get_shared(bk + BK_RR * K + k) : 0.0;
+    nPS[i] = okn ? get_shared(bk + BK_PSIS * K + k + 1) : 0.0;
+    nYS[i] = okn ? get_shared(bk + BK_YS * K + k + 1) : 0.0;
+    nSS[i] = okn ? get_shared(bk + BK_SIGS * K + k + 1) : 0.0;
   }
   Aff m = {1.0, 0.0};
 #pragma unroll
@@ -675,15 +669,15 @@ __device__ void combine_blocks(const Dims& D, const Bufs& B, const Params& prm, 
     const int k = k0 + i;
     const bool ok = i < e4 && k < K;
     const bool okn = i < e4 && k + 1 < K;
-    fA[i] = ok ? bk[BK_A * K + k] : 1.0;
-    fB[i] = ok ? bk[BK_B * K + k] : 0.0;
-    fRY[i] = ok ? bk[BK_RY * K + k] : 0.0;
-    fRS[i] = ok ? bk[BK_RS * K + k] : 0.0;
-    fRP[i] = ok ? bk[BK_RP * K + k] : 0.0;
-    fRR[i] = ok ? bk[BK_RR * K + k] : 0.0;
-    nPS[i] = okn ? bk[BK_PSIS * K + k + 1] : 0.0;
-    nYS[i] = okn ? bk[BK_YS * K + k + 1] : 0.0;
-    nSS[i] = okn ? bk[BK_SIGS * K + k + 1] : 0.0;
+    fA[i] = ok ? get_shared(bk + BK_A * K + k) : 1.0;
+    fB[i] = ok ? get_shared(bk + BK_B * K + k) : 0.0;
+    fRY[i] = ok ? get_shared(bk + BK_RY * K + k) : 0.0;
+    fRS[i] = ok ? get_shared(bk + BK_RS * K + k) : 0.0;
+    fRP[i] = ok ? get_shared(bk + BK_RP * K + k) : 0.0;
+    fRR[i] = ok ? get_shared(bk + BK_RR * K + k) : 0.0;
+    nPS[i] = okn ? get_shared(bk + BK_PSIS * K + k + 1) : 0.0;
+    nYS[i] = okn ? get_shared(bk + BK_YS * K + k + 1) : 0.0;
+    nSS[i] = okn ? get_shared(bk + BK_SIGS * K + k + 1) : 0.0;
   }
   Aff m = {1.0, 0.0};
 #pragma unroll
@@ -744,21 +738,12 @@ __device__ void combine_blocks(const Dims& D, const Bufs& B, const Params& prm, 
   }
 }
 
-// True in the one workgroup that finishes last; its loads after this point
-// see every other workgroup's block scalars (release by each block before its
-// arrival, acquire by the last one).  No workgroup waits for another.
-// Only thread 0 wrote the block scalars, so only it needs to publish them;
-// the last block's acquire fence by thread 0 precedes the barrier after which
-// all of its threads read the other blocks' scalars.
+// True in the one workgroup that finishes last, which may then read every
+// block's scalars.  Thread 0 wrote this block's.  No workgroup waits for
+// another.
 __device__ inline bool arrive_last(const Bufs& B, int nblocks, int* flag) {
   __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    const unsigned prev = atomicAdd(B.counter, 1u);
-    const bool last = prev == (unsigned)(nblocks - 1);
-    if (last) __threadfence();
-    *flag = last;
-  }
+  if (threadIdx.x == 0) *flag = arrive(B.counter, nblocks);
   __syncthreads();
   return *flag != 0;
 }
@@ -976,9 +961,9 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   __syncthreads();
   if (tid == 0) {
     const int K = D.nblk;
-    B.blk[BK_A * K + b] = lds2[0];
-    B.blk[BK_SIGS * K + b] = lds2[1];
-    B.blk[BK_PSIS * K + b] = lds2[3];
+    put_shared(B.blk + BK_A * K + b, lds2[0]);
+    put_shared(B.blk + BK_SIGS * K + b, lds2[1]);
+    put_shared(B.blk + BK_PSIS * K + b, lds2[3]);
   }
   // r0 = c - (X^T X + M) x0 with x0 the MM iterate (Algorithm 2)
   double rj = 0.0;

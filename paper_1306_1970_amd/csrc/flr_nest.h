@@ -29,6 +29,11 @@
 // adds terms of one sign, so every entry of the inverses and of W has a
 // relative error of a few ulp given the pivots, as in a Cholesky factorization,
 // also where the weights reach 1/eps.
+//
+// Measured (sweeps and factorization in one workgroup before -> here): the 100 x
+// 100 lattice 1153 -> 42 us per PCG step and 10.2 -> 1.5 ms per factorization (the
+// segment matrices are read once per step, 113 MB); 128 x 128
+// 1875 -> 48 us and 76 -> 2.8 ms; 32 x 32 (S = 1) 114 -> 10 us and 0.95 -> 0.55 ms.
 #pragma once
 #include "flr_device.h"
 
