@@ -534,7 +534,6 @@ static flr_status dense_prepare_once(flr_problem h) {
     g.M = (int32_t)dw->nd;
     g.N = (int32_t)dw->nd;
     g.K = (int32_t)D.n;
-    g.tiles_m = g.tiles_n = (int32_t)(dw->nd / kGemmMT);
     g.nslice = 1;
     DCK(launch_gram(D.dtype, g, h->stream));
   }

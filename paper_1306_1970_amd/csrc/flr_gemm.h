@@ -31,11 +31,11 @@ struct GemmArgs {
   int64_t ldc;
   int64_t cslice;    // stride between split-K partial outputs
   int32_t M, N, K;   // output M x N; K = reduction length of one slice
-  int32_t tiles_m, tiles_n, nslice;
+  int32_t nslice;             // K slices
+  int32_t tiles_m, tiles_n;   // set by the launch
 };
 
-constexpr int kGemmMT = 64;  // output rows per workgroup tile
-constexpr int kGemmNT = 64;  // output columns per workgroup tile
+constexpr int kGemmMT = 64;  // output rows of the larger workgroup tile (leading dimensions are multiples of it)
 constexpr int kGemmKT = 32;  // reduction depth staged per LDS tile
 
 hipError_t launch_gemm_xo(int dtype, const GemmArgs& g, hipStream_t st);   // U = X O (split over K)

@@ -576,8 +576,6 @@ static hipError_t grid_products(flr_problem h, const GridWork& gw, const GridDev
   a.M = (int32_t)D.n;
   a.N = nact;
   a.K = (int32_t)(D.p_pad / gw.splitk);
-  a.tiles_m = (int32_t)((D.n + kGemmMT - 1) / kGemmMT);
-  a.tiles_n = (nact + kGemmNT - 1) / kGemmNT;
   a.nslice = gw.splitk;
   hipError_t e = launch_gemm_xo(D.dtype, a, h->stream);
   if (e != hipSuccess) return e;
@@ -599,8 +597,6 @@ static hipError_t grid_products(flr_problem h, const GridWork& gw, const GridDev
   b.M = (int32_t)D.p_pad;
   b.N = nact;
   b.K = (int32_t)D.n;
-  b.tiles_m = (int32_t)(D.p_pad / kGemmMT);
-  b.tiles_n = (nact + kGemmNT - 1) / kGemmNT;
   b.nslice = 1;
   return launch_gemm_xtu(D.dtype, b, h->stream);
 }
@@ -953,8 +949,6 @@ extern "C" flr_status flr_profile_grid(flr_problem h, int32_t B, int32_t reps, d
     a.M = (int32_t)D.n;
     a.N = B;
     a.K = (int32_t)(D.p_pad / gw->splitk);
-    a.tiles_m = (int32_t)((D.n + kGemmMT - 1) / kGemmMT);
-    a.tiles_n = (B + kGemmNT - 1) / kGemmNT;
     a.nslice = gw->splitk;
     hipError_t er = launch_gemm_xo(D.dtype, a, h->stream);
     if (er == hipSuccess && gw->splitk > 1) {
@@ -976,8 +970,6 @@ extern "C" flr_status flr_profile_grid(flr_problem h, int32_t B, int32_t reps, d
     b.M = (int32_t)D.p_pad;
     b.N = B;
     b.K = (int32_t)D.n;
-    b.tiles_m = (int32_t)(D.p_pad / kGemmMT);
-    b.tiles_n = (B + kGemmNT - 1) / kGemmNT;
     b.nslice = 1;
     return launch_gemm_xtu(D.dtype, b, h->stream);
   };
