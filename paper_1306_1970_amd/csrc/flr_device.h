@@ -142,6 +142,41 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// (B v)_j for the weighted Laplacian of E, row j of its CSR: the first four
+// entries are requested at once and ahead of the values of v (a loop over the row
+// waits for its index and then for its value, entry by entry).  In steps, so that
+// a caller can put other work between the loads: rows(), entries(), then lap().
+struct EdgeRow {
+  int q0, q1;
+  int col[4];
+  double w[4];
+  __device__ inline void rows(const int32_t* __restrict__ rowptr, int64_t j) {
+    q0 = rowptr[j];
+    q1 = rowptr[j + 1];
+  }
+  // indices past the row stay inside the arrays (nnz >= 1 entries are allocated)
+  __device__ inline void entries(const int32_t* __restrict__ c, const double* __restrict__ ws, int64_t nnz) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int q = min(q0 + e, (int)nnz - 1);
+      col[e] = c[q];
+      w[e] = ws[q];
+    }
+  }
+  // sum over the row of w (v_j - v_k), in the row's order
+  __device__ inline double lap(const int32_t* __restrict__ c, const double* __restrict__ ws, const double* v,
+                               double vj) const {
+    double vk[4], s = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) vk[e] = v[col[e]];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (q0 + e < q1) s = fma(w[e], vj - vk[e], s);
+    for (int q = q0 + 4; q < q1; ++q) s = fma(ws[q], vj - v[c[q]], s);
+    return s;
+  }
+};
+
 // Affine map t -> a t + b.  compose(E, L) applies E first, then L.
 struct Aff {
   double a, b;
