@@ -560,7 +560,11 @@ __device__ inline int32_t next_phase(const Params& prm, State& o, int mode, doub
     o.rres = rn;
     return rr > 0.0 ? PH_CG : PH_END;
   }
-  const bool met = !(rn > prm.inner_tol);
+  // A refinement round that starts within 25 % of the tolerance aims at half of
+  // it: aiming at the tolerance itself, the FP32 products' error can leave the
+  // true residual just above, and the small cut would pass for a stall.
+  const bool close = prm.mixed && mode == CM_STEP && o.rres < 1.25 * prm.inner_tol;
+  const bool met = !(rn > (close ? 0.5 : 1.0) * prm.inner_tol);
   if (mode == CM_REFRESH) {
     const bool stalled = !(rn < 0.9 * o.rres);
     o.rres = rn;
