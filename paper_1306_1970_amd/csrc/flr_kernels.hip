@@ -765,41 +765,49 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
                                            State* __restrict__ sout, const Params* __restrict__ prmp,
                                            const int b) {
   constexpr int QMAX = 16;  // row panels whose partial products are prefetched
-  const State s = *sin;
   const int tid = threadIdx.x;
-  if (idle(s)) {
-    if (b == 0 && tid == 0) *sout = s;
-    return;
-  }
   const int64_t j = (int64_t)b * kBlk + tid;
   const bool real = j < D.p;
-  const Params prm = *prmp;
   __shared__ double lds[24];
   __shared__ double lds2[4];
   __shared__ double sh_L[kBlk + 1];
   __shared__ double sh_G[kMaxBlocks], sh_Z[kMaxBlocks];
   __shared__ int sh_flag;
 
-  if (s.phase == PH_CG) {
-    // every input of this step in one round of loads
-    const double* pv = B.pbuf + (int64_t)((s.cg_iter + 1) & 1) * D.p_pad;
-    double part = 0.0;
-    for (int q = tid; q < D.gridB; q += kWG) part += B.pqpart[q];
-    double qp[QMAX];
+  // every input of a PCG step in one round of loads, requested before the state
+  // that says whether this is one arrives (both parities of p)
+  // (indices clamped into range and the surplus dropped afterwards: a load under a
+  // condition is a branch around it)
+  const int64_t jc = min(j, D.p - 1);
+  double pq0 = B.pqpart[min(tid, D.gridB - 1)], pq1 = B.pqpart[min(tid + kWG, D.gridB - 1)];
+  double qp[QMAX];
 #pragma unroll
-    for (int rb = 0; rb < QMAX; ++rb) qp[rb] = (real && rb < D.rb2) ? B.qpart[(int64_t)rb * D.p_pad + j] : 0.0;
+  for (int rb = 0; rb < 4; ++rb) qp[rb] = B.qpart[(int64_t)min(rb, D.rb2 - 1) * D.p_pad + jc];
+  if (D.rb2 > 4) {
+#pragma unroll
+    for (int rb = 4; rb < QMAX; ++rb) qp[rb] = B.qpart[(int64_t)min(rb, D.rb2 - 1) * D.p_pad + jc];
+  } else {
+#pragma unroll
+    for (int rb = 4; rb < QMAX; ++rb) qp[rb] = 0.0;
+  }
+  const double pj0 = B.pbuf[jc], pj1 = B.pbuf[D.p_pad + jc], xj = B.x[jc], rj0 = B.r[jc];
+  double Lj = B.L[jc], invDj = B.invD[jc], sigj = B.sig[jc], psij = B.psi[jc];
+  const double Lnb = j + kBlk < D.p ? B.L[j + kBlk] : 0.0;  // thread 0: L of the next block's first element
+  const State s = *sin;
+  if (idle(s)) {
+    if (b == 0 && tid == 0) *sout = s;
+    return;
+  }
+  const Params prm = *prmp;
+  if (tid >= D.gridB) pq0 = 0.0;
+  if (tid + kWG >= D.gridB) pq1 = 0.0;
+  if (!real) Lj = invDj = sigj = psij = 0.0;
+
+  if (s.phase == PH_CG) {
+    const double pj = s.cg_iter & 1 ? pj0 : pj1;  // p of this step: parity (cg_iter + 1) & 1
+    double part = pq0 + pq1;
+    for (int q = tid + 2 * kWG; q < D.gridB; q += kWG) part += B.pqpart[q];
     const double qrest = real ? sum_parts(B.qpart + j, D.p_pad, QMAX, D.rb2) : 0.0;
-    double pj = 0.0, xj = 0.0, rj0 = 0.0, Lj = 0.0, invDj = 0.0, sigj = 0.0, psij = 0.0, Lnb = 0.0;
-    if (real) {
-      pj = pv[j];
-      xj = B.x[j];
-      rj0 = B.r[j];
-      Lj = B.L[j];
-      invDj = B.invD[j];
-      sigj = B.sig[j];
-      psij = B.psi[j];
-    }
-    if (tid == 0) Lnb = (j + kBlk < D.p) ? B.L[j + kBlk] : 0.0;
     const double pq = wg_sum(part, lds);
     const double nu = s.rz / pq;
     if (!(pq > 0.0) || !isfinite(nu)) {
@@ -815,7 +823,7 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
     if (real) {
       double q = 0.0;
 #pragma unroll
-      for (int rb = 0; rb < QMAX; ++rb) q += qp[rb];
+      for (int rb = 0; rb < QMAX; ++rb) q += rb < D.rb2 ? qp[rb] : 0.0;
       q += qrest;
       B.x[j] = fma(nu, pj, xj);
       rj = fma(-nu, q, rj0);
@@ -872,10 +880,8 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
       }
       return;
     }
-    const double sigj = real ? B.sig[j] : 0.0, psij = real ? B.psi[j] : 0.0;
-    const double Lj = real ? B.L[j] : 0.0, invDj = real ? B.invD[j] : 0.0;
     sh_L[tid] = Lj;
-    if (tid == 0) sh_L[kBlk] = (j + kBlk < D.p) ? B.L[j + kBlk] : 0.0;
+    if (tid == 0) sh_L[kBlk] = Lnb;
     __syncthreads();
     block_local_solve(D, B, b, j, rj, Lj, sh_L[tid + 1], invDj, sigj, psij, lds, lds2);
     if (arrive_last(B, D.nblk, &sh_flag)) {
@@ -940,19 +946,19 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   const double en = j + 1 < D.p ? B.e[j + 1] : 0.0;
   const double tin = B.mob[4 * (int64_t)D.nblk + b];
   const double tj = mob_apply(wg_scan_mob(mob_leaf(alj, ej), lds), tin);
-  const double invDj = real ? 1.0 / (tj + en) : 0.0;
+  invDj = real ? 1.0 / (tj + en) : 0.0;
   const double Lnext = real ? -en * invDj : 0.0;
   sh_L[tid + 1] = Lnext;
   if (tid == 0) sh_L[0] = ej > 0.0 ? -ej / (tin + ej) : 0.0;
   __syncthreads();
-  const double Lj = real ? sh_L[tid] : 0.0;
+  Lj = real ? sh_L[tid] : 0.0;
   // phi_j = prod_{i=start..j} (-L_i); psi_j = prod_{i=j+1..end+1} (-L_i);
   // sigma = zero-inflow backward sweep of phi / D
   const double phi = wg_scan_fwd({-Lj, 0.0}, lds).a;
   const double psi = wg_scan_rev({-Lnext, 0.0}, lds).a;
   const double sig = wg_scan_rev({-Lnext, phi * invDj}, lds).b;
-  const double psij = real ? psi : 0.0;
-  const double sigj = real ? sig : 0.0;
+  psij = real ? psi : 0.0;
+  sigj = real ? sig : 0.0;
   if (j < D.p_pad) {
     B.L[j] = Lj;
     B.invD[j] = invDj;
