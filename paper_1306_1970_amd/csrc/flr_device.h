@@ -105,21 +105,24 @@ __device__ inline bool arrive(unsigned* counter, int count) {
   return prev == (unsigned)(count - 1);
 }
 
-// Sum over the workgroup; every thread receives the result.  lds: 4 doubles.
+// The sums and scans below run over groups of 256 threads: the workgroup, or each
+// half of one of 512 (with LDS of its own; the barriers are the workgroup's).
+
+// Sum over the group; every thread receives the result.  lds: 4 doubles.
 __device__ inline double wg_sum(double v, double* lds) {
   v = wave_sum(v);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int w = (threadIdx.x >> 6) & 3, l = threadIdx.x & 63;
   __syncthreads();
   if (l == 0) lds[w] = v;
   __syncthreads();
   return (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
-// Four sums over the workgroup at once (one pair of barriers).  lds: 16 doubles.
+// Four sums over the group at once (one pair of barriers).  lds: 16 doubles.
 __device__ inline void wg_sum4(double* v, double* lds) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = wave_sum(v[k]);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int w = (threadIdx.x >> 6) & 3, l = threadIdx.x & 63;
   __syncthreads();
   if (l == 0) {
 #pragma unroll
@@ -186,7 +189,7 @@ __device__ inline Aff compose(Aff E, Aff Lm) { return {Lm.a * E.a, Lm.a * E.b + 
 // Inclusive scan in thread order 0..255 (recurrence t_j = a_j t_{j-1} + b_j).
 // lds: 8 doubles.
 __device__ inline Aff wg_scan_fwd(Aff m, double* lds) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     double pa = __shfl_up(m.a, d, 64), pb = __shfl_up(m.b, d, 64);
@@ -202,7 +205,7 @@ __device__ inline Aff wg_scan_fwd(Aff m, double* lds) {
 
 // Inclusive scan in thread order 255..0 (recurrence t_j = a_j t_{j+1} + b_j).
 __device__ inline Aff wg_scan_rev(Aff m, double* lds) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     double pa = __shfl_down(m.a, d, 64), pb = __shfl_down(m.b, d, 64);
@@ -268,7 +271,7 @@ __device__ inline double mob_apply(const Mob& m, double t) { return fma(m.a, t, 
 
 // Inclusive scan of the workgroup's maps in thread order 0..255.  lds: 16 doubles.
 __device__ inline Mob wg_scan_mob(Mob m, double* lds) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const Mob pm = {__shfl_up(m.a, d, 64), __shfl_up(m.b, d, 64), __shfl_up(m.c, d, 64), __shfl_up(m.d, d, 64)};

@@ -105,7 +105,7 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
     D.rb2 = 1;
     D.r2 = 0;
   }
-  D.nblk = (int32_t)(D.p_pad / kBlk);
+  D.nblk = (int32_t)((p + kBlk - 1) / kBlk);
   D.gridB = std::max(D.cb2 * D.rb2, D.nblk);
   D.nloss = flsa ? D.cb2 : D.rb2;
   return D;
@@ -698,7 +698,7 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   CK(dalloc(h, &B.losspart, (size_t)std::max(D.rb2, D.cb2)));
   CK(dalloc(h, &B.penpart, (size_t)D.nblk));
   CK(dalloc(h, &B.blk, (size_t)BK_N * (size_t)D.nblk));
-  CK(dalloc(h, &B.carry, 2 * (size_t)D.nblk));
+  CK(dalloc(h, &B.carry, 2 * (size_t)(D.p_pad / kBlk)));  // A reads them for the padding as well (times zero gains)
   CK(dalloc(h, &B.mob, 5 * (size_t)D.nblk));
   // M^-1 for graphs of bandwidth >= 2 (lattice, all-pairs)
   {

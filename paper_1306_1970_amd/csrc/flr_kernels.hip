@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kWG) void k_init(Dims D, Bufs B, const double* __re
     B.sig[j] = 0.0;
     B.psi[j] = 0.0;
   }
-  if (j < 2 * (int64_t)D.nblk) B.carry[j] = 0.0;
+  if (j < 2 * (D.p_pad / kBlk)) B.carry[j] = 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     State s;
     s.phase = PH_END;
@@ -508,14 +508,19 @@ __global__ __launch_bounds__(kWG) void k_gemv_b(Dims D, Bufs B, const State* __r
   gemv_b_body<XT, MX>(D, B, sin, sout, prmp, blockIdx.x);
 }
 
+// Solver blocks that one workgroup of the block kernel can take (groups of 256
+// threads).
+constexpr int kMaxGroup = 2;
+
 // Zero-inflow local solve of the block for the current residual r_j and the
 // block scalars that the next A launch combines into the global solution:
 //   forward  g_j = r_j - L_j g_{j-1}           (L D L^T, forward sweep)
 //   backward y_j = g_j / D_j - L_{j+1} y_{j+1}   (backward sweep)
+// loc (not null): the scalars stay in this workgroup's LDS (it holds every block).
 __device__ inline void block_local_solve(const Dims& D, const Bufs& B, int b, int64_t j, double rj, double Lj,
                                          double Lnext, double invDj, double sigj, double psij, double* lds,
-                                         double* lds2) {
-  const int tid = threadIdx.x;
+                                         double* lds2, double* loc) {
+  const int tid = threadIdx.x & (kBlk - 1);
   const Aff gf = wg_scan_fwd({-Lj, rj}, lds);
   const double g = gf.b;
   const Aff yb = wg_scan_rev({-Lnext, g * invDj}, lds);
@@ -527,13 +532,19 @@ __device__ inline void block_local_solve(const Dims& D, const Bufs& B, int b, in
   if (tid == 0) lds2[1] = yj;
   double sums[4] = {rj * yj, rj * sigj, rj * psij, rj * rj};
   wg_sum4(sums, lds);
-  if (tid == 0) {
-    put_shared(B.blk + BK_B * K + b, lds2[0]);
-    put_shared(B.blk + BK_YS * K + b, lds2[1]);
-    put_shared(B.blk + BK_RY * K + b, sums[0]);
-    put_shared(B.blk + BK_RS * K + b, sums[1]);
-    put_shared(B.blk + BK_RP * K + b, sums[2]);
-    put_shared(B.blk + BK_RR * K + b, sums[3]);
+  if (tid == 0 && b < K) {
+    auto put = [&](int field, double v) {
+      if (loc)
+        loc[field * kMaxGroup + b] = v;
+      else
+        put_shared(B.blk + field * K + b, v);
+    };
+    put(BK_B, lds2[0]);
+    put(BK_YS, lds2[1]);
+    put(BK_RY, sums[0]);
+    put(BK_RS, sums[1]);
+    put(BK_RP, sums[2]);
+    put(BK_RR, sums[3]);
   }
 }
 
@@ -575,15 +586,14 @@ __device__ inline int32_t next_phase(const Params& prm, State& o, int mode, doub
   return (met || !(rn > kRoundReduction * o.rres)) ? PH_RES : PH_CG;
 }
 
-// Wave-level variant of combine_blocks for K <= 256 (4 blocks per lane),
-// run by wave 0 alone: shuffles only, no barriers.
+// Wave-level variant of combine_blocks for K <= 64 E (E blocks per lane), run by
+// wave 0 alone: shuffles only, no barriers.  get(field, k): block scalars.
+template <int E, typename Get>
 __device__ void combine_blocks_wave(const Dims& D, const Bufs& B, const Params& prm, State o, double rz_prev,
-                                    int mode, State* __restrict__ sout) {
-  constexpr int E = 4;
+                                    int mode, State* __restrict__ sout, Get get) {
   const int l = threadIdx.x & 63;
   const int K = D.nblk;
   const int e = (K + 63) / 64;
-  const double* bk = B.blk;
   const int k0 = l * e;
   double fA[E], fB[E], fRY[E], fRS[E], fRP[E], fRR[E], nPS[E], nYS[E], nSS[E];
 #pragma unroll
@@ -591,15 +601,15 @@ __device__ void combine_blocks_wave(const Dims& D, const Bufs& B, const Params& 
     const int k = k0 + i;
     const bool ok = i < e && k < K;
     const bool okn = i < e && k + 1 < K;
-    fA[i] = ok ? get_shared(bk + BK_A * K + k) : 1.0;
-    fB[i] = ok ? get_shared(bk + BK_B * K + k) : 0.0;
-    fRY[i] = ok ? get_shared(bk + BK_RY * K + k) : 0.0;
-    fRS[i] = ok ? get_shared(bk + BK_RS * K + k) : 0.0;
-    fRP[i] = ok ? get_shared(bk + BK_RP * K + k) : 0.0;
-    fRR[i] = ok ? get_shared(bk + BK_RR * K + k) : 0.0;
-    nPS[i] = okn ? get_shared(bk + BK_PSIS * K + k + 1) : 0.0;
-    nYS[i] = okn ? get_shared(bk + BK_YS * K + k + 1) : 0.0;
-    nSS[i] = okn ? get_shared(bk + BK_SIGS * K + k + 1) : 0.0;
+    fA[i] = ok ? get(BK_A, k) : 1.0;
+    fB[i] = ok ? get(BK_B, k) : 0.0;
+    fRY[i] = ok ? get(BK_RY, k) : 0.0;
+    fRS[i] = ok ? get(BK_RS, k) : 0.0;
+    fRP[i] = ok ? get(BK_RP, k) : 0.0;
+    fRR[i] = ok ? get(BK_RR, k) : 0.0;
+    nPS[i] = okn ? get(BK_PSIS, k + 1) : 0.0;
+    nYS[i] = okn ? get(BK_YS, k + 1) : 0.0;
+    nSS[i] = okn ? get(BK_SIGS, k + 1) : 0.0;
   }
   Aff m = {1.0, 0.0};
 #pragma unroll
@@ -662,7 +672,7 @@ __device__ void combine_blocks_wave(const Dims& D, const Bufs& B, const Params& 
 __device__ void combine_blocks(const Dims& D, const Bufs& B, const Params& prm, State o, double rz_prev,
                                int mode, State* __restrict__ sout, double* sh_m, double* sh_G, double* sh_Z) {
   constexpr int EMAX = kMaxBlocks / kWG;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & (kWG - 1);  // a larger workgroup's groups do the same
   const int K = D.nblk;
   const int e4 = (K + kWG - 1) / kWG;
   const double* bk = B.blk;
@@ -761,18 +771,31 @@ __device__ inline bool arrive_last(const Bufs& B, int nblocks, int* flag) {
 // the B launch left for it), the gain vectors, r0 = c - Q x0 and its
 // local solve.  The last workgroup to finish combines the blocks.
 // ---------------------------------------------------------------------------
+//
+// VB blocks per workgroup, one per group of 256 threads, each with the arithmetic
+// of a workgroup of its own.  SOLO: one workgroup holds every block; their scalars
+// stay in LDS and it combines them itself, without the round trips of publishing
+// and arriving.
+template <int VB, bool SOLO>
 __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const State* __restrict__ sin,
                                            State* __restrict__ sout, const Params* __restrict__ prmp,
-                                           const int b) {
+                                           const int wg) {
   constexpr int QMAX = 16;  // row panels whose partial products are prefetched
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & (kBlk - 1);
+  const int vb = VB == 1 ? 0 : threadIdx.x >> 8;
+  const int b = wg * VB + vb;
   const int64_t j = (int64_t)b * kBlk + tid;
   const bool real = j < D.p;
-  __shared__ double lds[24];
-  __shared__ double lds2[4];
-  __shared__ double sh_L[kBlk + 1];
-  __shared__ double sh_G[kMaxBlocks], sh_Z[kMaxBlocks];
+  __shared__ double lds_g[VB][24];
+  __shared__ double lds2_g[VB][4];
+  __shared__ double sh_L_g[VB][kBlk + 1];
+  __shared__ double sh_G[SOLO ? 1 : kMaxBlocks], sh_Z[SOLO ? 1 : kMaxBlocks];
+  __shared__ double sh_blk[SOLO ? BK_N * kMaxGroup : 1];
   __shared__ int sh_flag;
+  double* lds = lds_g[vb];
+  double* lds2 = lds2_g[vb];
+  double* sh_L = sh_L_g[vb];
+  double* loc = SOLO ? sh_blk : nullptr;
 
   // every input of a PCG step in one round of loads, requested before the state
   // that says whether this is one arrives (both parities of p)
@@ -793,6 +816,34 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   const double pj0 = B.pbuf[jc], pj1 = B.pbuf[D.p_pad + jc], xj = B.x[jc], rj0 = B.r[jc];
   double Lj = B.L[jc], invDj = B.invD[jc], sigj = B.sig[jc], psij = B.psi[jc];
   const double Lnb = j + kBlk < D.p ? B.L[j + kBlk] : 0.0;  // thread 0: L of the next block's first element
+  // SOLO: the scalars that stay for the whole MM step, for lane k of the combining wave
+  double kA = 0.0, kSS = 0.0, kPS = 0.0;
+  if (SOLO) {
+    const int k = min((int)(threadIdx.x & 63), D.nblk - 1), kn = min(k + 1, D.nblk - 1);
+    kA = B.blk[BK_A * D.nblk + k];
+    kSS = B.blk[BK_SIGS * D.nblk + kn];
+    kPS = B.blk[BK_PSIS * D.nblk + kn];
+  }
+  // the last workgroup to finish combines the blocks (SOLO: the only one)
+  auto combine = [&](State o, double rz_prev, int mode) {
+    if constexpr (SOLO) {
+      __syncthreads();
+      if (threadIdx.x < 64)
+        combine_blocks_wave<1>(D, B, *prmp, o, rz_prev, mode, sout, [&](int field, int k) {
+          const bool kept = field == BK_A || field == BK_SIGS || field == BK_PSIS;
+          if (kept && mode != CM_FIRST) return field == BK_A ? kA : field == BK_SIGS ? kSS : kPS;
+          return sh_blk[field * kMaxGroup + k];
+        });
+    } else if (arrive_last(B, (D.nblk + VB - 1) / VB, &sh_flag)) {
+      const double* bk = B.blk;
+      const int K = D.nblk;
+      if (K > 4 * 64)
+        combine_blocks(D, B, *prmp, o, rz_prev, mode, sout, lds, sh_G, sh_Z);
+      else if (threadIdx.x < 64)
+        combine_blocks_wave<4>(D, B, *prmp, o, rz_prev, mode, sout,
+                            [&](int field, int k) { return get_shared(bk + field * K + k); });
+    }
+  };
   const State s = *sin;
   if (idle(s)) {
     if (b == 0 && tid == 0) *sout = s;
@@ -842,18 +893,12 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
     sh_L[tid] = Lj;
     if (tid == 0) sh_L[kBlk] = Lnb;
     __syncthreads();
-    block_local_solve(D, B, b, j, rj, Lj, sh_L[tid + 1], invDj, sigj, psij, lds, lds2);
-    if (arrive_last(B, D.nblk, &sh_flag)) {
-      State o = s;
-      o.cg_iter = s.cg_iter + 1;
-      o.cg_total = s.cg_total + 1;
-      o.nu = nu;
-      if (D.nblk <= 4 * 64) {
-        if (tid < 64) combine_blocks_wave(D, B, prm, o, s.rz, CM_STEP, sout);
-      } else {
-        combine_blocks(D, B, prm, o, s.rz, CM_STEP, sout, lds, sh_G, sh_Z);
-      }
-    }
+    block_local_solve(D, B, b, j, rj, Lj, sh_L[tid + 1], invDj, sigj, psij, lds, lds2, loc);
+    State o = s;
+    o.cg_iter = s.cg_iter + 1;
+    o.cg_total = s.cg_total + 1;
+    o.nu = nu;
+    combine(o, s.rz, CM_STEP);
     return;
   }
 
@@ -883,14 +928,8 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
     sh_L[tid] = Lj;
     if (tid == 0) sh_L[kBlk] = Lnb;
     __syncthreads();
-    block_local_solve(D, B, b, j, rj, Lj, sh_L[tid + 1], invDj, sigj, psij, lds, lds2);
-    if (arrive_last(B, D.nblk, &sh_flag)) {
-      if (D.nblk <= 4 * 64) {
-        if (tid < 64) combine_blocks_wave(D, B, prm, s, 0.0, CM_REFRESH, sout);
-      } else {
-        combine_blocks(D, B, prm, s, 0.0, CM_REFRESH, sout, lds, sh_G, sh_Z);
-      }
-    }
+    block_local_solve(D, B, b, j, rj, Lj, sh_L[tid + 1], invDj, sigj, psij, lds, lds2, loc);
+    combine(s, 0.0, CM_REFRESH);
     return;
   }
   // f(b) = loss + penalties (identical arithmetic in every workgroup)
@@ -944,7 +983,7 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   const bool inpad = j < D.p_pad;
   const double alj = inpad ? B.d[j] : 1.0, ej = inpad ? B.e[j] : 0.0;
   const double en = j + 1 < D.p ? B.e[j + 1] : 0.0;
-  const double tin = B.mob[4 * (int64_t)D.nblk + b];
+  const double tin = B.mob[4 * (int64_t)D.nblk + min(b, D.nblk - 1)];
   const double tj = mob_apply(wg_scan_mob(mob_leaf(alj, ej), lds), tin);
   invDj = real ? 1.0 / (tj + en) : 0.0;
   const double Lnext = real ? -en * invDj : 0.0;
@@ -969,11 +1008,16 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
   if (tid == kBlk - 1) lds2[0] = phi;
   if (tid == 0) { lds2[1] = sigj; lds2[3] = psij; }
   __syncthreads();
-  if (tid == 0) {
+  if (tid == 0 && b < D.nblk) {
     const int K = D.nblk;
     put_shared(B.blk + BK_A * K + b, lds2[0]);
     put_shared(B.blk + BK_SIGS * K + b, lds2[1]);
     put_shared(B.blk + BK_PSIS * K + b, lds2[3]);
+    if (loc) {
+      loc[BK_A * kMaxGroup + b] = lds2[0];
+      loc[BK_SIGS * kMaxGroup + b] = lds2[1];
+      loc[BK_PSIS * kMaxGroup + b] = lds2[3];
+    }
   }
   // r0 = c - (X^T X + M) x0 with x0 the MM iterate (Algorithm 2)
   double rj = 0.0;
@@ -981,19 +1025,14 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
     rj = cj - (qsum + apply_m(B, prm, j, B.x));
     B.r[j] = rj;
   }
-  block_local_solve(D, B, b, j, rj, Lj, Lnext, invDj, sigj, psij, lds, lds2);
-  if (arrive_last(B, D.nblk, &sh_flag)) {
-    if (D.nblk <= 4 * 64) {
-      if (tid < 64) combine_blocks_wave(D, B, prm, o, 0.0, CM_FIRST, sout);
-    } else {
-      combine_blocks(D, B, prm, o, 0.0, CM_FIRST, sout, lds, sh_G, sh_Z);
-    }
-  }
+  block_local_solve(D, B, b, j, rj, Lj, Lnext, invDj, sigj, psij, lds, lds2, loc);
+  combine(o, 0.0, CM_FIRST);
 }
 
-__global__ __launch_bounds__(kWG) void k_block(Dims D, Bufs B, const State* __restrict__ sin,
-                                               State* __restrict__ sout, const Params* __restrict__ prmp) {
-  block_body(D, B, sin, sout, prmp, blockIdx.x);
+template <int VB, bool SOLO>
+__global__ __launch_bounds__(kBlk * VB) void k_block(Dims D, Bufs B, const State* __restrict__ sin,
+                                                     State* __restrict__ sout, const Params* __restrict__ prmp) {
+  block_body<VB, SOLO>(D, B, sin, sout, prmp, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1179,7 +1218,7 @@ __global__ __launch_bounds__(kWG) void k_gemv_b_grp(const GroupEntry* __restrict
 
 __global__ __launch_bounds__(kWG) void k_block_grp(const GroupEntry* __restrict__ e, int count, int par) {
   const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, LN_C)];
-  block_body(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm, (int)blockIdx.x - g.wg_c);
+  block_body<1, false>(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm, (int)blockIdx.x - g.wg_c);
 }
 
 __global__ __launch_bounds__(kWG) void k_band_grp(const GroupEntry* __restrict__ e, int par) {
@@ -1270,7 +1309,19 @@ static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, const GroupEnt
       hipLaunchKernelGGL((k_gemv_b<XT, MX>), dim3(D.gridB), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
       break;
     case LN_C:
-      hipLaunchKernelGGL(k_block, dim3(D.nblk), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
+      // one or two blocks (p <= 512) in one workgroup, which combines them without the
+      // device round trips (8.5 -> 7.0 us at p = 200; four in one of 1024 threads
+      // were slower, its scans share one CU's LDS); two per workgroup where the
+      // arrivals of as many workgroups as blocks bound the launch (13.6 -> 12.9 us at
+      // 391 blocks)
+      if (D.nblk == 1)
+        hipLaunchKernelGGL((k_block<1, true>), dim3(1), dim3(kBlk), 0, st, D, B, sin, sout, B.prm);
+      else if (D.nblk == 2)
+        hipLaunchKernelGGL((k_block<2, true>), dim3(1), dim3(2 * kBlk), 0, st, D, B, sin, sout, B.prm);
+      else if (D.nblk >= 128)
+        hipLaunchKernelGGL((k_block<2, false>), dim3((D.nblk + 1) / 2), dim3(2 * kBlk), 0, st, D, B, sin, sout, B.prm);
+      else
+        hipLaunchKernelGGL((k_block<1, false>), dim3(D.nblk), dim3(kBlk), 0, st, D, B, sin, sout, B.prm);
       break;
     case LN_BAND:
       hipLaunchKernelGGL(k_band, dim3(1), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
