@@ -1,6 +1,7 @@
-"""The tridiagonal factor of M as a scan of Moebius maps: sizes at the edges of
-a solver block (256), of a grid chunk (2048) and of the two-level scan (more
-than 256 blocks), broken chains (no coupling at some indexes) and weights that
+"""The tridiagonal factor of M as a scan of Moebius maps and the block kernel's
+variants: sizes at the edges of a solver block (256), of the one workgroup that
+holds two (512), of two blocks per workgroup (128 blocks, an odd number of them),
+of a grid chunk (2048) and of the two-level scan (more than 256 blocks), broken chains (no coupling at some indexes) and weights that
 span sixteen decades.
 
 X = I, so Q = I + M is tridiagonal and every MM iterate follows from a direct
@@ -92,8 +93,9 @@ def _reference(y, e):
     return b, cg
 
 
-@pytest.mark.parametrize("p,broken", [(2, False), (9, True), (255, False), (256, True), (257, False), (2048, False),
-                                      (2049, True), (5000, False), (66000, True)])
+@pytest.mark.parametrize("p,broken", [(2, False), (9, True), (255, False), (256, True), (257, False), (512, True),
+                                      (513, False), (2048, False), (2049, True), (5000, False), (32513, True),
+                                      (32769, False), (66000, True)])
 def test_scan_factor(flr, ctx, p, broken):
     y, e = _case(p, broken)
     print("chain p=%d broken=%s" % (p, broken), flush=True)
