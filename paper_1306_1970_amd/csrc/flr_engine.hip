@@ -20,8 +20,7 @@
 #include "flr_problem.h"
 
 namespace flr {
-hipError_t launch_rotation(const Dims& D, const Bufs& B, const GroupEntry* self, int par, int which, hipStream_t st,
-                           bool mixed);
+hipError_t launch_rotation(const Dims& D, const Bufs& B, int par, int which, hipStream_t st, bool mixed);
 hipError_t launch_setup(const Dims& D, const void* X, const double* y, double* cpart, double* spart, double* c,
                         double* s, hipStream_t st);
 hipError_t launch_init(const Dims& D, const Bufs& B, const double* warm, int use_warm, hipStream_t st);
@@ -168,7 +167,6 @@ std::vector<int> round_launches(bool factor, bool nest, bool nest_tops) {
   if (factor) v.push_back(LN_BAND);
   if (nest) v.push_back(LN_NEST1);
   if (nest_tops) v.insert(v.end(), {LN_NEST2, LN_NEST3});
-  if (nest) v.push_back(LN_NEST4);
   return v;
 }
 
@@ -195,7 +193,7 @@ flr_status build_graph(flr_problem h, bool mixed, bool band) {
   const std::vector<int> round = round_launches(band && !S, band && S, band && S > 1);
   const int per = (int)round.size();
   for (int i = 0; i < per * kRounds && err == hipSuccess; ++i)
-    err = launch_rotation(h->D, h->B, h->d_self, i & 1, round[(size_t)(i % per)], h->stream, mixed);
+    err = launch_rotation(h->D, h->B, i & 1, round[(size_t)(i % per)], h->stream, mixed);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(h->stream, &g);
   if (err != hipSuccess) return fail(FLR_ERR_DEVICE, std::string("capture launch: ") + hipGetErrorString(err));
@@ -735,16 +733,6 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   B.c = c;
   B.s = s;
   B.prm = h->d_prm;
-  if (B.nest.S) {
-    CK(dalloc(h, &h->d_self, 1));
-    GroupEntry self{};
-    self.D = D;
-    self.B = B;
-    self.wgs_k = B.nest.wgs;
-    self.band = BAND_NEST;
-    CK(hipMemcpyAsync(h->d_self, &self, sizeof(self), hipMemcpyHostToDevice, h->stream));
-    CK(hipStreamSynchronize(h->stream));  // the copy's source goes out of scope
-  }
   CK(hipMemcpyAsync(yd, y, (size_t)n * sizeof(double), hipMemcpyHostToDevice, h->stream));
   CK(hipMemcpyAsync(rp, rowptr.data(), rowptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
   CK(hipMemcpyAsync(cl, col.data(), col.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
@@ -939,7 +927,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   HIP_OR_FAIL(hipEventCreate(&e2));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 0, 0, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 0, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
@@ -947,14 +935,14 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   float ms_a = 0.f;
   // re-time A from its own start event
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 0, 0, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 0, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   HIP_OR_FAIL(hipEventElapsedTime(&ms_a, e0, e1));
   float ms_b = 0.f;
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 1, 1, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 1, 1, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e2, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   HIP_OR_FAIL(hipEventElapsedTime(&ms_b, e1, e2));
@@ -968,7 +956,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   float ms_c = 0.f;
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, h->d_self, 0, 2, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 2, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e2, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.x, save, vb, hipMemcpyDeviceToDevice, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.r, save + h->D.p_pad, vb, hipMemcpyDeviceToDevice, h->stream));

@@ -3,7 +3,7 @@
 // One solve is a device-resident state machine.  Every launch is one of three
 // kernels that run in a fixed rotation A, B, C (a hipGraph holds S rounds);
 // when M is banded with bandwidth >= 2 further launches after C apply M^-1: K1
-// to K4 through nested dense inverses (flr_nest.h), or K through its banded
+// to K3 through nested dense inverses (flr_nest.h), or K through its banded
 // Cholesky factor (flr_band.h) where those would need too much memory:
 //   A  row-panel GEMV   u = X v            (v = new CG direction, or the MM iterate)
 //   B  column-panel GEMV q = X^T u (+ M v)  (plus, at an MM boundary: objective
@@ -38,7 +38,7 @@ constexpr int kMaxBlocks = 1024;  // max solver blocks -> p_pad <= 262144
 enum Phase : int32_t { PH_CG = 0, PH_END = 1, PH_DONE = 2, PH_BANDMM = 3, PH_RES = 4, PH_BANDRES = 5, PH_BANDSOLVE = 6 };
 
 // Launches of a rotation, in their order within a round.
-enum Launch : int { LN_A = 0, LN_B = 1, LN_C = 2, LN_BAND = 3, LN_NEST1 = 4, LN_NEST2 = 5, LN_NEST3 = 6, LN_NEST4 = 7 };
+enum Launch : int { LN_A = 0, LN_B = 1, LN_C = 2, LN_BAND = 3, LN_NEST1 = 4, LN_NEST2 = 5, LN_NEST3 = 6 };
 
 // What a combine of the block scalars follows: a PCG step, the first residual
 // of an MM step, or a residual refreshed in FP64 (refinement).
@@ -72,7 +72,8 @@ struct State {
   int64_t cg_total;
   double rz, f_old, f_new, rel_change, rel_res, nu, gamma;
   double rres;  // relative FP64 residual at the last MM boundary or refresh (mixed precision)
-  int32_t fstage, pad;  // PH_BANDMM with nested inverses: factorization stages done
+  int32_t fstage;  // PH_BANDMM with nested inverses: factorization stages done
+  int32_t fin;     // 1: M^-1 r has been applied, the next A sums its shares of r^T z and r^T r
 };
 
 struct Dims {

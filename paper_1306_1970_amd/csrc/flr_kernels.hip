@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kWG) void k_init(Dims D, Bufs B, const double* __re
     s.gamma = 0.0;
     s.rres = 0.0;
     s.fstage = 0;
-    s.pad = 0;
+    s.fin = 0;
     B.st[0] = s;
     B.st[1] = s;
   }
@@ -174,24 +174,100 @@ __device__ inline void rows_a(const Dims& D, const Bufs& B, const XT* Xb, int cb
 // Nothing to do for A, B and C: done, or M is being factored by later launches.
 __device__ inline bool idle(const State& s) { return s.phase == PH_DONE || s.phase == PH_BANDMM; }
 
+// Reduction of the true residual that one refinement round asks of the
+// FP32-product PCG (its products carry errors near 1e-7 relative, so it
+// cannot be trusted much further in one round).
+constexpr double kRoundReduction = 1e-4;
+
+// Phase after a new residual (its squared norm rr, relative norm rn); also
+// records the FP64 residual of a boundary or refresh in o.rres.
+// Algorithm 2's inner loop is repeat-until: after the first residual of an
+// MM step at least one PCG step runs unless that residual is exactly zero (nu
+// would be 0/0).  After a PCG step the inner test decides.  With FP32
+// products (mixed precision) a round of PCG stops once its recursive residual
+// is kRoundReduction below the round's FP64 starting residual (or meets the
+// inner tolerance); then the true residual c - Q x is recomputed in FP64 and
+// the MM step ends only if that passes the inner test - else PCG restarts
+// from it (iterative refinement).  Refinement also ends when a refresh has
+// cut the true residual by less than 10 % (FP32 products can resolve no more
+// on this system) or at the PCG step cap.
+__device__ __forceinline__ int32_t next_phase(const Params& prm, State& o, int mode, double rr, double rn) {
+  const bool capped = o.cg_iter >= prm.max_cg;
+  if (mode == CM_FIRST) {
+    o.rres = rn;
+    return rr > 0.0 ? PH_CG : PH_END;
+  }
+  // A refinement round that starts within 25 % of the tolerance aims at half of
+  // it: aiming at the tolerance itself, the FP32 products' error can leave the
+  // true residual just above, and the small cut would pass for a stall.
+  const bool close = prm.mixed && mode == CM_STEP && o.rres < 1.25 * prm.inner_tol;
+  const bool met = !(rn > (close ? 0.5 : 1.0) * prm.inner_tol);
+  if (mode == CM_REFRESH) {
+    const bool stalled = !(rn < 0.9 * o.rres);
+    o.rres = rn;
+    return (met || capped || stalled) ? PH_END : PH_CG;
+  }
+  if (capped) return PH_END;
+  if (!prm.mixed) return met ? PH_END : PH_CG;
+  return (met || !(rn > kRoundReduction * o.rres)) ? PH_RES : PH_CG;
+}
+
+// The end of a step whose M^-1 r came from K1..K3 (flr_nest.h): every workgroup of
+// the next A sums the shares of r^T z and r^T r in the same order and takes the
+// inner stopping test and gamma for itself.  The loads are issued with the state's
+// and before any of X; as a launch of one workgroup of its own this took 4.2 us, here
+// 1.1 (a PCG step of the 32 x 32 lattice 28.3 -> 25.2 us, of the 100 x 100 one 96 -> 93).
+__device__ __forceinline__ void nest_finish(const Bufs& B, State& s) {
+  __shared__ double red[16];
+  double sums[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int q = threadIdx.x; q < B.nest.nparts; q += kWG) {
+    sums[0] += B.nest.part[2 * q];
+    sums[1] += B.nest.part[2 * q + 1];
+  }
+  if (!__builtin_amdgcn_readfirstlane(s.fin)) return;
+  wg_sum4(sums, red);
+  const Params prm = *B.prm;
+  const double rz_prev = s.rz, rn = sqrt(sums[1]) / prm.cnorm;
+  const int mode = s.phase == PH_BANDSOLVE ? CM_FIRST : s.phase == PH_BANDRES ? CM_REFRESH : CM_STEP;
+  s.phase = __builtin_amdgcn_readfirstlane(next_phase(prm, s, mode, sums[1], rn));
+  s.rel_res = rn;
+  s.gamma = mode != CM_STEP ? 0.0 : sums[0] / rz_prev;
+  s.rz = sums[0];
+  s.fin = 0;
+}
+
 // ---------------------------------------------------------------------------
 // A: row-panel GEMV u_part[cb] = X[rb, cb] v[cb].  In a PCG step v is the new
 // direction p = z + gamma p_old, where z = M^-1 r is rebuilt from the local
 // block solutions and the carries that the last C workgroup combined
 // (z_j = y_j + sigma_j G_k + psi_j Z_k).  Once PCG has converged, or at the
 // MM boundary, v is the iterate x.  The state is read through a restrict
-// pointer (scalar loads), so it does not wait behind the X loads.
+// pointer (scalar loads), so it does not wait behind the X loads.  NEST: M^-1 may
+// come from nested inverses (B.nest.S > 0), whose step this launch ends.
 // ---------------------------------------------------------------------------
-template <typename XT, bool MX>
+template <typename XT, bool MX, bool NEST>
 __device__ __forceinline__ void gemv_a_body(const Dims& D, const Bufs& B, const State* __restrict__ sin,
                                             State* __restrict__ sout, const int wg) {
   constexpr int V = XV<XT>::V;
   constexpr int NV = 4;  // 16-byte loads per lane per row (the panel is 256 V columns)
   using RAW = typename XV<XT>::raw;
-  const State s = *sin;
+  State s = *sin;
+  if (NEST && B.nest.S) nest_finish(B, s);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cb = wg % D.cb1, rb = wg / D.cb1;
-  if (wg == 0 && tid == 0) *sout = s;
+  if (wg == 0 && tid == 0) {
+    State o = *sin;  // read again, so that s stays in registers
+    if (NEST) {
+      o.phase = s.phase;
+      o.fin = s.fin;
+      o.rz = s.rz;
+      o.gamma = s.gamma;
+      o.rel_res = s.rel_res;
+      o.rres = s.rres;
+    }
+    *sout = o;
+  }
   if (idle(s)) return;
   const int64_t c0 = (int64_t)cb * D.c1;
   const int64_t r0 = (int64_t)rb * D.r1, r1 = min<int64_t>(D.n, r0 + D.r1);
@@ -253,10 +329,10 @@ __device__ __forceinline__ void gemv_a_body(const Dims& D, const Bufs& B, const 
     rows_a<XT, double>(D, B, Xb, cb, r0, r1, c0, lane, wave, sh_v, cur0, cur1);
 }
 
-template <typename XT, bool MX>
+template <typename XT, bool MX, bool NEST>
 __global__ __launch_bounds__(kWG) void k_gemv_a(Dims D, Bufs B, const State* __restrict__ sin,
                                                 State* __restrict__ sout) {
-  gemv_a_body<XT, MX>(D, B, sin, sout, blockIdx.x);
+  gemv_a_body<XT, MX, NEST>(D, B, sin, sout, blockIdx.x);
 }
 
 // (M v)_j = lambda1 a_j v_j + lambda2 sum_k w_jk (v_j - v_k)  (A and B of the linear system)
@@ -546,44 +622,6 @@ __device__ inline void block_local_solve(const Dims& D, const Bufs& B, int b, in
     put(BK_RP, sums[2]);
     put(BK_RR, sums[3]);
   }
-}
-
-// Reduction of the true residual that one refinement round asks of the
-// FP32-product PCG (its products carry errors near 1e-7 relative, so it
-// cannot be trusted much further in one round).
-constexpr double kRoundReduction = 1e-4;
-
-// Phase after a new residual (its squared norm rr, relative norm rn); also
-// records the FP64 residual of a boundary or refresh in o.rres.
-// Algorithm 2's inner loop is repeat-until: after the first residual of an
-// MM step at least one PCG step runs unless that residual is exactly zero (nu
-// would be 0/0).  After a PCG step the inner test decides.  With FP32
-// products (mixed precision) a round of PCG stops once its recursive residual
-// is kRoundReduction below the round's FP64 starting residual (or meets the
-// inner tolerance); then the true residual c - Q x is recomputed in FP64 and
-// the MM step ends only if that passes the inner test - else PCG restarts
-// from it (iterative refinement).  Refinement also ends when a refresh has
-// cut the true residual by less than 10 % (FP32 products can resolve no more
-// on this system) or at the PCG step cap.
-__device__ inline int32_t next_phase(const Params& prm, State& o, int mode, double rr, double rn) {
-  const bool capped = o.cg_iter >= prm.max_cg;
-  if (mode == CM_FIRST) {
-    o.rres = rn;
-    return rr > 0.0 ? PH_CG : PH_END;
-  }
-  // A refinement round that starts within 25 % of the tolerance aims at half of
-  // it: aiming at the tolerance itself, the FP32 products' error can leave the
-  // true residual just above, and the small cut would pass for a stall.
-  const bool close = prm.mixed && mode == CM_STEP && o.rres < 1.25 * prm.inner_tol;
-  const bool met = !(rn > (close ? 0.5 : 1.0) * prm.inner_tol);
-  if (mode == CM_REFRESH) {
-    const bool stalled = !(rn < 0.9 * o.rres);
-    o.rres = rn;
-    return (met || capped || stalled) ? PH_END : PH_CG;
-  }
-  if (capped) return PH_END;
-  if (!prm.mixed) return met ? PH_END : PH_CG;
-  return (met || !(rn > kRoundReduction * o.rres)) ? PH_RES : PH_CG;
 }
 
 // Wave-level variant of combine_blocks for K <= 64 E (E blocks per lane), run by
@@ -1093,10 +1131,11 @@ __global__ __launch_bounds__(kWG) void k_band(Dims D, Bufs B, const State* __res
 }
 
 // ---------------------------------------------------------------------------
-// K1..K4 (banded M through nested inverses, flr_nest.h).  In the factorization
-// phase each of K1..K3 does the next stage; with all stages done K1 starts the
-// solve for the new residual.  K4 sums r^T z and r^T r and takes the inner
-// stopping test and gamma, as K does.
+// K1..K3 (banded M through nested inverses, flr_nest.h).  In the factorization
+// phase each does the next stage; with all stages done K1 starts the solve for
+// the new residual.  They leave shares of r^T z and r^T r, which the next A sums
+// (nest_finish).  Summed by their last workgroup to arrive instead, a step of the
+// 32 x 32 lattice took 32 us against 26: hundreds of arrivals at one counter.
 // ---------------------------------------------------------------------------
 template <int WHICH>
 __device__ __forceinline__ void nest_body(const NestView& B, const State* __restrict__ sin, State* __restrict__ sout,
@@ -1130,12 +1169,15 @@ __device__ __forceinline__ void nest_body(const NestView& B, const State* __rest
       return;
     }
   }
+  const bool solve = s.phase != PH_DONE && s.phase != PH_END && s.phase != PH_RES;
   if (lead) {
     State o = s;
     if (s.phase == PH_BANDMM) o.phase = PH_BANDSOLVE;
+    // K1 without separators or K3 ends the step
+    if (solve && WHICH == (B.nest.S == 1 ? LN_NEST1 : LN_NEST3)) o.fin = 1;
     *sout = o;
   }
-  if (s.phase == PH_DONE || s.phase == PH_END || s.phase == PH_RES) return;
+  if (!solve) return;
   if (WHICH == LN_NEST1) {
     if (B.nest.cols == 16)
       nest_apply_segments<16>(B, wg, lds);
@@ -1148,35 +1190,6 @@ __device__ __forceinline__ void nest_body(const NestView& B, const State* __rest
       nest_apply_back<16>(B, wg, lds);
     else
       nest_apply_back<32>(B, wg, lds);
-  }
-}
-
-__device__ __forceinline__ void nest_finish(const Bufs& B, const State* __restrict__ sin, State* __restrict__ sout,
-                                            const Params* __restrict__ prmp) {
-  __shared__ double red[24];
-  const State s = *sin;
-  const int tid = threadIdx.x;
-  if (s.phase != PH_CG && s.phase != PH_BANDSOLVE && s.phase != PH_BANDRES) {
-    if (tid == 0) *sout = s;
-    return;
-  }
-  double rzp = 0.0, rrp = 0.0;
-  for (int q = tid; q < B.nest.nparts; q += kWG) {
-    rzp += B.nest.part[2 * q];
-    rrp += B.nest.part[2 * q + 1];
-  }
-  double sums[4] = {rzp, rrp, 0.0, 0.0};
-  wg_sum4(sums, red);
-  if (tid == 0) {
-    const Params prm = *prmp;
-    State o = s;
-    const double rz = sums[0], rn = sqrt(sums[1]) / prm.cnorm;
-    const int mode = s.phase == PH_BANDSOLVE ? CM_FIRST : s.phase == PH_BANDRES ? CM_REFRESH : CM_STEP;
-    o.phase = next_phase(prm, o, mode, sums[1], rn);
-    o.rel_res = rn;
-    o.gamma = mode != CM_STEP ? 0.0 : rz / s.rz;
-    o.rz = rz;
-    *sout = o;
   }
 }
 
@@ -1207,7 +1220,7 @@ __device__ inline int group_of(const GroupEntry* __restrict__ e, int count, int 
 template <typename XT, bool MX>
 __global__ __launch_bounds__(kWG) void k_gemv_a_grp(const GroupEntry* __restrict__ e, int count, int par) {
   const GroupEntry& g = e[group_of(e, count, (int)blockIdx.x, LN_A)];
-  gemv_a_body<XT, MX>(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), (int)blockIdx.x - g.wg_a);
+  gemv_a_body<XT, MX, true>(g.D, g.B, g.B.st + par, g.B.st + (par ^ 1), (int)blockIdx.x - g.wg_a);
 }
 
 template <typename XT, bool MX>
@@ -1247,15 +1260,6 @@ __global__ __launch_bounds__(kNT, 2) void k_nest_grp(const GroupEntry* __restric
   nest_body<WHICH>(v, g.B.st + par, g.B.st + (par ^ 1), g.B.prm, (int)blockIdx.x - g.wg_k);
 }
 
-__global__ __launch_bounds__(kWG) void k_nest_finish_grp(const GroupEntry* __restrict__ e, int par) {
-  const GroupEntry& g = e[blockIdx.x];
-  if (g.band != BAND_NEST) {
-    if (threadIdx.x == 0) g.B.st[par ^ 1] = g.B.st[par];
-    return;
-  }
-  nest_finish(g.B, g.B.st + par, g.B.st + (par ^ 1), g.B.prm);
-}
-
 // State of every problem of a batch after a graph launch (slot 0 of each).
 __global__ __launch_bounds__(kWG) void k_gather_states(const GroupEntry* __restrict__ e, int count,
                                                        State* __restrict__ out) {
@@ -1273,8 +1277,7 @@ static hipError_t launch_grouped_t(const GroupEntry* e, int count, int wgs, int 
     case LN_BAND: hipLaunchKernelGGL(k_band_grp, dim3(count), dim3(kWG), 0, st, e, par); break;
     case LN_NEST1: hipLaunchKernelGGL(k_nest_grp<LN_NEST1>, g, dim3(kNT), 0, st, e, count, par); break;
     case LN_NEST2: hipLaunchKernelGGL(k_nest_grp<LN_NEST2>, g, dim3(kNT), 0, st, e, count, par); break;
-    case LN_NEST3: hipLaunchKernelGGL(k_nest_grp<LN_NEST3>, g, dim3(kNT), 0, st, e, count, par); break;
-    default: hipLaunchKernelGGL(k_nest_finish_grp, dim3(count), dim3(kWG), 0, st, e, par); break;
+    default: hipLaunchKernelGGL(k_nest_grp<LN_NEST3>, g, dim3(kNT), 0, st, e, count, par); break;
   }
   return hipGetLastError();
 }
@@ -1297,13 +1300,15 @@ hipError_t launch_gather_states(const GroupEntry* e, int count, State* out, hipS
 }
 
 template <typename XT, bool MX>
-static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, const GroupEntry* self, int par, int which,
-                                    hipStream_t st) {
+static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, int par, int which, hipStream_t st) {
   const State* sin = B.st + par;
   State* sout = B.st + (par ^ 1);
   switch (which) {
     case LN_A:
-      hipLaunchKernelGGL((k_gemv_a<XT, MX>), dim3(D.cb1 * D.rb1), dim3(kWG), 0, st, D, B, sin, sout);
+      if (B.nest.S)
+        hipLaunchKernelGGL((k_gemv_a<XT, MX, true>), dim3(D.cb1 * D.rb1), dim3(kWG), 0, st, D, B, sin, sout);
+      else
+        hipLaunchKernelGGL((k_gemv_a<XT, MX, false>), dim3(D.cb1 * D.rb1), dim3(kWG), 0, st, D, B, sin, sout);
       break;
     case LN_B:
       hipLaunchKernelGGL((k_gemv_b<XT, MX>), dim3(D.gridB), dim3(kWG), 0, st, D, B, sin, sout, B.prm);
@@ -1332,26 +1337,21 @@ static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, const GroupEnt
     case LN_NEST2:
       hipLaunchKernelGGL(k_nest<LN_NEST2>, dim3(B.nest.wgs), dim3(kNT), 0, st, nest_view(D, B), sin, sout, B.prm);
       break;
-    case LN_NEST3:
-      hipLaunchKernelGGL(k_nest<LN_NEST3>, dim3(B.nest.wgs), dim3(kNT), 0, st, nest_view(D, B), sin, sout, B.prm);
-      break;
     default:
-      hipLaunchKernelGGL(k_nest_finish_grp, dim3(1), dim3(kWG), 0, st, self, par);
+      hipLaunchKernelGGL(k_nest<LN_NEST3>, dim3(B.nest.wgs), dim3(kNT), 0, st, nest_view(D, B), sin, sout, B.prm);
       break;
   }
   return hipGetLastError();
 }
 
-// self: the problem's own entry in device memory (the K1..K4 launches).
-hipError_t launch_rotation(const Dims& D, const Bufs& B, const GroupEntry* self, int par, int which, hipStream_t st,
-                           bool mixed) {
+hipError_t launch_rotation(const Dims& D, const Bufs& B, int par, int which, hipStream_t st, bool mixed) {
   switch (D.dtype) {
-    case 0: return mixed ? launch_rotation_t<double, true>(D, B, self, par, which, st)
-                         : launch_rotation_t<double, false>(D, B, self, par, which, st);
-    case 1: return mixed ? launch_rotation_t<float, true>(D, B, self, par, which, st)
-                         : launch_rotation_t<float, false>(D, B, self, par, which, st);
-    default: return mixed ? launch_rotation_t<uint16_t, true>(D, B, self, par, which, st)
-                          : launch_rotation_t<uint16_t, false>(D, B, self, par, which, st);
+    case 0: return mixed ? launch_rotation_t<double, true>(D, B, par, which, st)
+                         : launch_rotation_t<double, false>(D, B, par, which, st);
+    case 1: return mixed ? launch_rotation_t<float, true>(D, B, par, which, st)
+                         : launch_rotation_t<float, false>(D, B, par, which, st);
+    default: return mixed ? launch_rotation_t<uint16_t, true>(D, B, par, which, st)
+                          : launch_rotation_t<uint16_t, false>(D, B, par, which, st);
   }
 }
 

@@ -11,8 +11,9 @@
 //   z_I = M_II^-1 r_I - W z_s
 // is three launches of matrix-vector products without any chain:
 //   K1  M_II^-1 r_I and W^T r_I, segment by segment;  K2  T^-1 (..);  K3  z_I.
-// S = 1 (no separators) leaves K1 alone.  S is chosen on the host by the bytes
-// of one apply and the work of one factorization (nest_plan).
+// S = 1 (no separators) leaves K1 alone.  The next A sums r^T z and r^T r.  S is
+// chosen on the host by the bytes of one apply and the work of one factorization
+// (nest_plan).
 //
 // The inverses come from the symmetric block sweep (Gauss-Jordan) with pivot
 // blocks of 64 on the bordered segment matrices [M_II M_Is; M_sI 0], which

@@ -43,7 +43,6 @@ struct flr_problem_s {
   hipEvent_t ev[2] = {nullptr, nullptr};
   hipGraph_t graph[2][2] = {};         // [mixed][banded]
   hipGraphExec_t gexec[2][2] = {};
-  flr::GroupEntry* d_self = nullptr;    // this problem as the only entry of a grouped launch (nested inverses)
   int band_w = 0;                       // bandwidth + 1 of E when the banded factor is allocated, else 0
   std::vector<void*> allocs;
   size_t footprint = 0;
