@@ -161,6 +161,22 @@ Nest nest_plan(int64_t p, int64_t bw) {
   return best;
 }
 
+// Device memory of the nested inverses; on failure none is kept.
+hipError_t nest_alloc(flr_problem h, Nest& Q) {
+  const size_t mark = h->allocs.size(), bytes = h->footprint;
+  hipError_t e = dalloc(h, &Q.seg, (size_t)Q.S * (size_t)Q.N * (size_t)Q.N);
+  if (e == hipSuccess) e = dalloc(h, &Q.top, (size_t)Q.ntp * (size_t)Q.ntp);
+  if (e == hipSuccess) e = dalloc(h, &Q.pan, 2 * (size_t)Q.pans * kTE);
+  if (e == hipSuccess) e = dalloc(h, &Q.dinv, 2 * (size_t)Q.S * kTE);
+  if (e == hipSuccess) e = dalloc(h, &Q.gpart, (size_t)Q.S * (size_t)Q.bt * kTile);
+  if (e == hipSuccess) e = dalloc(h, &Q.part, 2 * (size_t)Q.nparts);
+  if (e != hipSuccess) {
+    for (; h->allocs.size() > mark; h->allocs.pop_back()) (void)hipFree(h->allocs.back());
+    h->footprint = bytes;
+  }
+  return e;
+}
+
 // Launches of one round of the rotation (Launch values), by how M is applied.
 std::vector<int> round_launches(bool factor, bool nest, bool nest_tops) {
   std::vector<int> v = {LN_A, LN_B, LN_C};
@@ -705,15 +721,16 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
     const int64_t W = bw + 1;
     if (bw >= 2 && W <= kBandMaxW && (double)p * (double)W * 8.0 <= 4.0 * (1 << 30)) {
       B.nest = nest_plan(p, bw);
-      Nest& Q = B.nest;
-      if (Q.S) {
-        CK(dalloc(h, &Q.seg, (size_t)Q.S * (size_t)Q.N * (size_t)Q.N));
-        CK(dalloc(h, &Q.top, (size_t)Q.ntp * (size_t)Q.ntp));
-        CK(dalloc(h, &Q.pan, 2 * (size_t)Q.pans * kTE));
-        CK(dalloc(h, &Q.dinv, 2 * (size_t)Q.S * kTE));
-        CK(dalloc(h, &Q.gpart, (size_t)Q.S * (size_t)Q.bt * kTile));
-        CK(dalloc(h, &Q.part, 2 * (size_t)Q.nparts));
-      } else {
+      if (B.nest.S) {
+        const hipError_t e = nest_alloc(h, B.nest);
+        if (e == hipErrorOutOfMemory) {
+          (void)hipGetLastError();
+          B.nest = Nest{};  // the band factor (q = 224 lattice: 0.18 GB against 1.3) may still fit
+        } else {
+          CK(e);
+        }
+      }
+      if (!B.nest.S) {
         CK(dalloc(h, &B.Lb, (size_t)p * (size_t)W));
         CK(dalloc(h, &B.LbT, (size_t)p * (size_t)W));
         CK(dalloc(h, &B.invdb, (size_t)D.p_pad));

@@ -3,7 +3,8 @@ single solve and the blocked sweeps of the grid, at sizes where they can go
 wrong: orders around one tile (64), segments with a short last one, separators
 that straddle tiles, bandwidths at both ends of each block size of the sweeps
 (W = bw + 1 = 16 .. 31, 32 .. 63, 64 .. 107) and just outside, orders that leave
-a short last block.
+a short last block; and one order whose inverses would pass 4 GB, where the single
+solve keeps the band factor.
 
 X = I, so Q = I + M is banded and every MM iterate follows from a banded
 Cholesky solve.  Bar: 1e-8 of max |beta| (the FP64 bar of the parity tests), and
@@ -93,7 +94,7 @@ def _check(what, beta, n, ref, cg):
 
 
 @pytest.mark.parametrize("p,bw", [(4, 2), (63, 5), (64, 63), (65, 64), (129, 17), (1000, 999), (1600, 2), (1901, 43),
-                                  (2300, 70), (4099, 64), (4900, 130)])
+                                  (2300, 70), (4099, 64), (4900, 130), (250001, 3)])
 def test_single(flr, ctx, p, bw):
     y, e = _case(p, bw)
     print("single p=%d bw=%d" % (p, bw), flush=True)
