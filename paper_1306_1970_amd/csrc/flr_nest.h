@@ -32,10 +32,12 @@
 // also where the weights reach 1/eps.
 //
 // Measured (sweeps and factorization in one workgroup before -> here): the 100 x
-// 100 lattice 1153 -> 42 us per PCG step and 10.2 -> 1.5 ms per factorization (the
+// 100 lattice 1153 -> 26 us per PCG step and 10.2 -> 1.1 ms per factorization (the
 // segment matrices are read once per step, 113 MB); 128 x 128
-// 1875 -> 48 us and 76 -> 2.8 ms; 32 x 32 (S = 1) 114 -> 10 us and 0.95 -> 0.55 ms.
+// 1875 -> 38 us and 76 -> 2.2 ms; 32 x 32 (S = 1) 114 -> 6 us and 0.95 -> 0.39 ms.
 #pragma once
+#include <utility>
+
 #include "flr_device.h"
 
 namespace flr {
@@ -93,40 +95,104 @@ __device__ inline int64_t nest_sep_global(const Nest& Q, int a) {
   return nest_first(Q, s) + Q.m + (a - s * Q.bw);
 }
 
-// Inverse of the symmetric positive definite 64 x 64 tile in A (row stride
-// kTLd), into out (row-major, ld 64): the sweep one pivot at a time, wave w
-// holding columns 8 w .. 8 w + 7, lane l row l; per pivot the owner publishes
-// the pivot column (by symmetry also the pivot row) through LDS.  Bound by that
-// round trip.  Clears nothing on failure: *bad is set on a pivot that is not
-// positive and finite.  buf: 2 x 64 doubles of LDS outside A.
-__device__ inline void nest_invert(int tid, const double* A, double* __restrict__ out, double* buf, unsigned* bad) {
-  const int lane = tid & 63, wave = tid >> 6;
-  double a[8];
+// One pivot of the sweep of a 16 x 16 block held by one wave: lane l has row
+// 4 (l & 3) + (l >> 2 & 3), columns 4 (l >> 4) .. + 3 (as the first operand of an
+// FP64 MFMA).  The pivot row comes to every lane of its 16 by a row broadcast, the
+// pivot column (by symmetry) from its lanes by permlane swaps: no LDS, no barrier.
+template <int K>
+__device__ __forceinline__ void nest_pivot(int lane, double (&x)[4], bool& ok) {
+  constexpr int kg = K >> 2, kc = K & 3, at = 4 * kc + kg;  // the row's lane among 16
+  double row[4];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) a[c] = A[lane * kTLd + 8 * wave + c];
-  bool ok = true;
-  for (int w0 = 0; w0 < 8; ++w0) {
+  for (int c = 0; c < 4; ++c) row[c] = dpp_f64<0x150 + at>(x[c]);  // row_newbcast
+  const double piv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x[kc]), 16 * kg + at),
+                                      __builtin_amdgcn_readlane(__double2loint(x[kc]), 16 * kg + at));
+  const auto l16 = __builtin_amdgcn_permlane16_swap(__double2loint(x[kc]), __double2loint(x[kc]), false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(__double2hiint(x[kc]), __double2hiint(x[kc]), false, false);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(l16[kg & 1], l16[kg & 1], false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(h16[kg & 1], h16[kg & 1], false, false);
+  const double col = __hiloint2double((int)h32[kg >> 1], (int)l32[kg >> 1]);
+  ok = ok && piv > 0.0 && isfinite(piv);
+  const double d = 1.0 / piv;
+  const bool mine = (lane & 15) == at;
+  const double t = mine ? -d : col * d;
 #pragma unroll
-    for (int c0 = 0; c0 < 8; ++c0) {
-      const int k = 8 * w0 + c0;
-      double* col = buf + (k & 1) * kTile;
-      if (wave == w0) col[lane] = a[c0];
-      lds_barrier();
-      const double piv = col[k], ci = col[lane];
-      ok = ok && piv > 0.0 && isfinite(piv);
-      const double d = 1.0 / piv, t = ci * d;
-      const bool mine = lane == k;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const double cj = col[8 * wave + c];
-        a[c] = mine ? cj * d : fma(-t, cj, a[c]);
-      }
-      if (wave == w0) a[c0] = mine ? -d : t;
+  for (int c = 0; c < 4; ++c) x[c] = fma(-t, row[c], mine ? 0.0 : x[c]);
+  if ((lane >> 4) == kg) x[kc] = t;
+}
+template <int... K>
+__device__ __forceinline__ void nest_sweep16(int lane, double (&x)[4], bool& ok, std::integer_sequence<int, K...>) {
+  (nest_pivot<K>(lane, x, ok), ...);
+}
+
+// Inverse of the symmetric positive definite 64 x 64 tile in P (row stride kTLd;
+// Q is a second such tile, both are overwritten), into out (row-major, ld 64): the
+// sweep in pivot blocks of 16.  Wave 0 sweeps the diagonal block in its registers;
+// then wave w forms blocks (w / 2, 2 (w & 1) + {0, 1}) of the result, A_ij - (A_ik D)
+// A_kj, on the matrix cores, A_ik D as the transpose of D A_ki, whose layout is the
+// second product's operand.  The chain of 64 pivots bounds it: with every pivot
+// column published through LDS (a barrier and an LDS round trip each) 17 us, a stage
+// of the 32 x 32 lattice 31, here 10 and 24; and the launches' registers, which that
+// form set, went from 171 to 99 (K1 of the 100 x 100 lattice 16.5 -> 11.8 us).  *bad is set on a pivot that is not positive and finite.
+__device__ inline void nest_invert(int tid, double* P, double* Q, double* __restrict__ out, unsigned* bad) {
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g4 = (lane >> 4) * 4, i16 = lane & 15, sig = 4 * (i16 & 3) + (i16 >> 2);
+  const int i = wave >> 1;
+#pragma unroll 1
+  for (int k = 0; k < 4; ++k) {
+    const int kk = 16 * k * (kTLd + 1) + sig * kTLd + g4;  // this lane's part of the diagonal block
+    if (wave == 0) {
+      nx4 v = *reinterpret_cast<const nx4*>(P + kk);
+      double x[4] = {v[0], v[1], v[2], v[3]};
+      bool ok = true;
+      nest_sweep16(lane, x, ok, std::make_integer_sequence<int, 16>());
+      *reinterpret_cast<nx4*>(Q + kk) = nx4{x[0], x[1], x[2], x[3]};  // -D
+      if (!ok && lane == 0) *bad = 1u;
     }
-  }
-  if (!ok && tid == 0) *bad = 1u;  // the same decision in every thread
+    __syncthreads();
+    const nx4 d = *reinterpret_cast<const nx4*>(Q + kk);
+    nx4 u = {0.0, 0.0, 0.0, 0.0};  // -(A_ik D)[i16][g4 ..]
+    if (i != k) {
+      const nx4 a = *reinterpret_cast<const nx4*>(P + (16 * i + i16) * kTLd + 16 * k + g4);
 #pragma unroll
-  for (int c = 0; c < 8; ++c) out[lane * kTile + 8 * wave + c] = -a[c];
+      for (int c = 0; c < 4; ++c) u = __builtin_amdgcn_mfma_f64_16x16x4f64(d[c], a[c], u, 0, 0, 0);
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int j = 2 * (wave & 1) + b;
+      if (i == k && j == k) continue;  // wave 0 has written it
+      if (j == k) {
+        *reinterpret_cast<nx4*>(Q + (16 * i + i16) * kTLd + 16 * k + g4) = -u;
+        continue;
+      }
+      const nx4 a = *reinterpret_cast<const nx4*>(P + (16 * j + i16) * kTLd + 16 * k + g4);  // A_kj transposed
+      if (i == k) {
+        nx4 v = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v = __builtin_amdgcn_mfma_f64_16x16x4f64(d[c], a[c], v, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Q[(16 * i + g4 + r) * kTLd + 16 * j + i16] = -v[r];
+      } else {
+        const int at = (16 * i + (lane >> 4)) * kTLd + 16 * j + i16;  // rows lane / 16 + 4 r
+        nx4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = P[at + 4 * r * kTLd];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v = __builtin_amdgcn_mfma_f64_16x16x4f64(u[c], a[c], v, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Q[at + 4 * r * kTLd] = v[r];
+      }
+    }
+    __syncthreads();
+    double* s = P;
+    P = Q;
+    Q = s;
+  }
+#pragma unroll
+  for (int q = 0; q < kTE / kNT; ++q) {
+    const int e = tid + kNT * q;
+    out[e] = -P[(e >> 6) * kTLd + (e & 63)];
+  }
 }
 
 // 64 x 64 product P[m][n] = sum_k A[m][k] Bm[n][k] of two LDS tiles: wave w
@@ -356,7 +422,7 @@ __device__ inline void nest_stage(const NestView& B, double lam2, int stage, int
 #pragma unroll
           for (int r = 0; r < 4; ++r) LA[(m0 + r) * kTLd + n0 + 16 * b] = v[b][r];
         __syncthreads();
-        nest_invert(tid, LA, d1 + (int64_t)mat * kTE, LB, B.counter + 32);
+        nest_invert(tid, LA, LB, d1 + (int64_t)mat * kTE, B.counter + 32);
       } else if (j == next) {
 #pragma unroll
         for (int b = 0; b < 2; ++b)
