@@ -72,10 +72,12 @@ typedef enum { FLR_PREC_FP64 = 0, FLR_PREC_MIXED_FP32 = 1 } flr_precision;
 
 /* Preconditioner of the PCG inner solve (Algorithm 2 uses M = lambda1 A +
  * lambda2 B itself).
- *   BAND    M exactly, through its banded Cholesky factor (bandwidth
- *           bw = max |j - k| over E; section 3.1): for bw >= 2, i.e. the 2-D
- *           lattice (bw = q) and all-pairs fusion; one factorization per MM
- *           iteration, two sequential triangular sweeps per PCG step.
+ *   BAND    M exactly (bandwidth bw = max |j - k| over E; section 3.1): for
+ *           bw >= 2, i.e. the 2-D lattice (bw = q) and all-pairs fusion.  One
+ *           factorization per MM iteration: nested dense inverses in the single
+ *           solves and the ragged batch (matrix-vector products per PCG step;
+ *           the banded Cholesky factor where their memory does not fit), the
+ *           banded Cholesky factor and two triangular sweeps in the grid.
  *           Needs lambda1 > 0 and bw + 1 <= 1025.
  *   TRIDIAG the tridiagonal part of M (edges (j-1, j) keep their coupling,
  *           every other edge adds only to the diagonal): exactly M for the

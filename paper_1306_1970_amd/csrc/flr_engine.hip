@@ -115,7 +115,7 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
 // factorization and 40 applies.  The model, in us: an apply costs its bytes at
 // 4.5 TB/s and 3 (S = 1) or 9 (three launches); a stage 14 (the inversion of the
 // next pivot block) or its tiles at 3.4 us of matrix-core time per CU.  The
-// minimum is flat: twice the stage times (measured, 24 to 40) move S by one or
+// minimum is flat: twice the stage times (measured, 24 to 31) move S by one or
 // two.  Small orders stay whole (S = 1 up to p of about 1100); 100 x 100 gives
 // S = 15, 128 x 128 S = 19.  S = 0, the band factor in
 // one workgroup instead, where the matrices pass 4 GB (the band factor's own

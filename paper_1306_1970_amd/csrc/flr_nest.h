@@ -34,7 +34,7 @@
 // Measured (sweeps and factorization in one workgroup before -> here): the 100 x
 // 100 lattice 1153 -> 26 us per PCG step and 10.2 -> 1.1 ms per factorization (the
 // segment matrices are read once per step, 113 MB); 128 x 128
-// 1875 -> 38 us and 76 -> 2.2 ms; 32 x 32 (S = 1) 114 -> 6 us and 0.95 -> 0.39 ms.
+// 1875 -> 38 us and 76 -> 2.0 ms; 32 x 32 (S = 1) 114 -> 6 us and 0.95 -> 0.39 ms.
 #pragma once
 #include <utility>
 
