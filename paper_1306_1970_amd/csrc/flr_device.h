@@ -95,12 +95,19 @@ __device__ inline void put_shared(double* p, double v) {
 __device__ inline double get_shared(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Called by the one thread that published with put_shared; true for the last
-// of `count` arrivals, which may then read every publisher's values.
+// The wave's own stores have completed.  A barrier does not wait for another
+// wave's, so where several waves publish each calls this before the barrier that
+// precedes arrive().
+__device__ inline void published() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // gfx9 encoding: vmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+}
+// Called by one thread after everything its workgroup published has completed (its
+// own wave's stores are waited for here); true for the last of `count` arrivals,
+// which may then read every publisher's values.
 __device__ inline bool arrive(unsigned* counter, int count) {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_s_waitcnt(0x0f70);  // gfx9 encoding: vmcnt(0), this thread's stores have completed
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  published();
   const unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return prev == (unsigned)(count - 1);
 }

@@ -791,9 +791,11 @@ __device__ void combine_blocks(const Dims& D, const Bufs& B, const Params& prm, 
 }
 
 // True in the one workgroup that finishes last, which may then read every
-// block's scalars.  Thread 0 wrote this block's.  No workgroup waits for
-// another.
+// block's scalars.  The first thread of each group of 256 wrote its block's; thread
+// 0 arrives for all VB of them.  No workgroup waits for another.
+template <int VB>
 __device__ inline bool arrive_last(const Bufs& B, int nblocks, int* flag) {
+  if (VB > 1) published();  // thread 256 publishes from another wave than the one that arrives
   __syncthreads();
   if (threadIdx.x == 0) *flag = arrive(B.counter, nblocks);
   __syncthreads();
@@ -872,7 +874,7 @@ __device__ __forceinline__ void block_body(const Dims& D, const Bufs& B, const S
           if (kept && mode != CM_FIRST) return field == BK_A ? kA : field == BK_SIGS ? kSS : kPS;
           return sh_blk[field * kMaxGroup + k];
         });
-    } else if (arrive_last(B, (D.nblk + VB - 1) / VB, &sh_flag)) {
+    } else if (arrive_last<VB>(B, (D.nblk + VB - 1) / VB, &sh_flag)) {
       const double* bk = B.blk;
       const int K = D.nblk;
       if (K > 4 * 64)
@@ -1317,8 +1319,9 @@ static hipError_t launch_rotation_t(const Dims& D, const Bufs& B, int par, int w
       // one or two blocks (p <= 512) in one workgroup, which combines them without the
       // device round trips (8.5 -> 7.0 us at p = 200; four in one of 1024 threads
       // were slower, its scans share one CU's LDS); two per workgroup where the
-      // arrivals of as many workgroups as blocks bound the launch (13.6 -> 12.9 us at
-      // 391 blocks)
+      // arrivals of as many workgroups as blocks bound the launch (one and two per
+      // workgroup: 8.4 and 8.9 us at 64 blocks, 9.1 and 9.1 at 96, 9.5 and 9.3 at 128,
+      // 12.0 and 10.8 at 256, 13.8 and 13.4 at 391, 15.3 and 14.2 at 512)
       if (D.nblk == 1)
         hipLaunchKernelGGL((k_block<1, true>), dim3(1), dim3(kBlk), 0, st, D, B, sin, sout, B.prm);
       else if (D.nblk == 2)
