@@ -259,8 +259,15 @@ __device__ inline Aff wave_scan_rev(Aff m) {
 struct Mob {
   double a, b, c, d;  // t -> (a t + b) / (c t + d), all >= 0
 };
+// Exactness has an end: with lambda1 below 1e-16 lambda2 the exact M is singular to
+// working precision, M^-1 as large as 1 / lambda1 and PCG with it breaks down, while
+// the textbook form's own rounding kept the pivots near half an ulp of the couplings.
+// alpha gets that as its least value (lambda1 = 1e-30, p = 1500, X = I: 6000 steps to
+// the cap and a wrong iterate without, 3500 with it, 3780 with the textbook form);
+// where lambda1 / |b| is above 1e-16 lambda2 / eps no value changes.
 __device__ inline Mob mob_leaf(double alpha, double e) {
   if (!(e > 0.0)) return {0.0, alpha, 0.0, 1.0};  // no coupling: the map is constant
+  alpha = fmax(alpha, 0x1p-53 * e);
   if (e >= 1.0) return {alpha / e + 1.0, alpha, 1.0 / e, 1.0};
   return {alpha + e, alpha * e, 1.0, e};
 }
