@@ -76,8 +76,9 @@ typedef enum { FLR_PREC_FP64 = 0, FLR_PREC_MIXED_FP32 = 1 } flr_precision;
  *           bw >= 2, i.e. the 2-D lattice (bw = q) and all-pairs fusion.  One
  *           factorization per MM iteration: nested dense inverses in the single
  *           solves and the ragged batch (matrix-vector products per PCG step;
- *           the banded Cholesky factor where their memory does not fit), the
- *           banded Cholesky factor and two triangular sweeps in the grid.
+ *           their memory is taken by the first such solve if at most a quarter
+ *           of what is free, else the banded Cholesky factor), the banded
+ *           Cholesky factor and two triangular sweeps in the grid.
  *           Needs lambda1 > 0 and bw + 1 <= 1025.
  *   TRIDIAG the tridiagonal part of M (edges (j-1, j) keep their coupling,
  *           every other edge adds only to the diagonal): exactly M for the
@@ -240,14 +241,17 @@ flr_status flr_solve_batch(const flr_problem* problems, int32_t count, const dou
                            const double* lambda2, double tol, const flr_solve_opts* opts, double* const* beta_out,
                            flr_result* res);
 
-/* Device footprint of a problem in bytes (what serving admission charges). */
+/* Device footprint of a problem in bytes: what the handle holds now (it grows with
+ * the first grid, Algorithm 1 or nested-inverse solve). */
 flr_status flr_problem_footprint(flr_problem h, size_t* bytes);
 int64_t flr_problem_n(flr_problem h);
 int64_t flr_problem_p(flr_problem h);
 int64_t flr_problem_m(flr_problem h);
 
 /* Serving: requests are admitted while the sum of the footprints of problems
- * in flight stays within hbm_budget_bytes and a slot is free; each slot runs
+ * in flight stays within hbm_budget_bytes and a slot is free (a solve that may use
+ * nested inverses counts with their memory where hbm_budget_bytes can hold both,
+ * else it uses the banded factor and counts without); each slot runs
  * on its own stream, so solves that arrive while others run overlap on the
  * device.  Results do not depend on what else runs (fixed reduction trees,
  * no cross-request atomics). */

@@ -485,11 +485,14 @@ static flr_status dense_prepare_once(flr_problem h);
 
 static flr_status dense_prepare(flr_problem h) {
   if (h->dense) return FLR_OK;
-  const flr_status st = dense_prepare_once(h);
-  if (st != FLR_OK) {
-    (void)hipStreamSynchronize(h->stream);
-    dense_free(h);
-  }
+  flr_status st;
+  do {  // a second time without the memory that a single solve's inverses hold
+    st = dense_prepare_once(h);
+    if (st != FLR_OK) {
+      (void)hipStreamSynchronize(h->stream);
+      dense_free(h);
+    }
+  } while (st == FLR_ERR_OUT_OF_MEMORY && nest_release(h));
   return st;
 }
 

@@ -161,20 +161,46 @@ Nest nest_plan(int64_t p, int64_t bw) {
   return best;
 }
 
-// Device memory of the nested inverses; on failure none is kept.
-hipError_t nest_alloc(flr_problem h, Nest& Q) {
-  const size_t mark = h->allocs.size(), bytes = h->footprint;
-  hipError_t e = dalloc(h, &Q.seg, (size_t)Q.S * (size_t)Q.N * (size_t)Q.N);
-  if (e == hipSuccess) e = dalloc(h, &Q.top, (size_t)Q.ntp * (size_t)Q.ntp);
-  if (e == hipSuccess) e = dalloc(h, &Q.pan, 2 * (size_t)Q.pans * kTE);
-  if (e == hipSuccess) e = dalloc(h, &Q.dinv, 2 * (size_t)Q.S * kTE);
-  if (e == hipSuccess) e = dalloc(h, &Q.gpart, (size_t)Q.S * (size_t)Q.bt * kTile);
-  if (e == hipSuccess) e = dalloc(h, &Q.part, 2 * (size_t)Q.nparts);
-  if (e != hipSuccess) {
-    for (; h->allocs.size() > mark; h->allocs.pop_back()) (void)hipFree(h->allocs.back());
-    h->footprint = bytes;
+// Carves the buffers of the nested inverses out of one block (base null: sizes
+// only) and returns their bytes.
+size_t nest_carve(Nest& Q, char* base) {
+  size_t used = 0;
+  auto take = [&](double** p, size_t count) {
+    *p = base ? reinterpret_cast<double*>(base + used) : nullptr;
+    used += (count * sizeof(double) + 255) / 256 * 256;
+  };
+  take(&Q.seg, (size_t)Q.S * (size_t)Q.N * (size_t)Q.N);
+  take(&Q.top, (size_t)Q.ntp * (size_t)Q.ntp);
+  take(&Q.pan, 2 * (size_t)Q.pans * kTE);
+  take(&Q.dinv, 2 * (size_t)Q.S * kTE);
+  take(&Q.gpart, (size_t)Q.S * (size_t)Q.bt * kTile);
+  take(&Q.part, 2 * (size_t)Q.nparts);
+  return used;
+}
+
+// The nested inverses' memory, on the first solve that applies them: a handle used
+// only for grids, Algorithm 1 or with another preconditioner does without.  They
+// take several times the band factor's bytes, so no more than a quarter of what is
+// free is taken for them; false where that is not enough or the allocation fails,
+// and the solve applies M^-1 through the band factor.
+bool nest_ready(flr_problem h) {
+  if (h->nest_mem) return true;
+  size_t free_bytes = 0, total = 0;
+  void* mem = nullptr;
+  if (!h->nest.S || hipMemGetInfo(&free_bytes, &total) != hipSuccess || h->nest_bytes > free_bytes / 4 ||
+      hipMalloc(&mem, h->nest_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
   }
-  return e;
+  if (hipMemsetAsync(mem, 0, h->nest_bytes, h->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(mem);
+    return false;
+  }
+  nest_carve(h->nest, static_cast<char*>(mem));
+  h->nest_mem = mem;
+  h->nest_held = true;
+  return true;
 }
 
 // Launches of one round of the rotation (Launch values), by how M is applied.
@@ -186,8 +212,12 @@ std::vector<int> round_launches(bool factor, bool nest, bool nest_tops) {
   return v;
 }
 
-BandMode band_mode(flr_problem h) {
-  return !h->h_prm->band ? BAND_NONE : h->B.nest.S ? BAND_NEST : BAND_FACTOR;
+// The buffers of the current (last) solve; the nested inverses' only where it uses
+// them and they have not been released since.
+Bufs solve_bufs(flr_problem h) {
+  Bufs B = h->B;
+  if (h->band_mode == BAND_NEST && h->nest_mem) B.nest = h->nest;
+  return B;
 }
 
 bool is_device_ptr(const void* ptr) {
@@ -199,17 +229,17 @@ bool is_device_ptr(const void* ptr) {
   return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
 }
 
-flr_status build_graph(flr_problem h, bool mixed, bool band) {
-  hipGraphExec_t& ge = h->gexec[mixed][band];
-  hipGraph_t& gr = h->graph[mixed][band];
+flr_status build_graph(flr_problem h, bool mixed) {
+  hipGraphExec_t& ge = h->gexec[mixed][h->band_mode];
+  hipGraph_t& gr = h->graph[mixed][h->band_mode];
   if (ge) return FLR_OK;
   HIP_OR_FAIL(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
   hipError_t err = hipSuccess;
-  const int S = h->B.nest.S;
-  const std::vector<int> round = round_launches(band && !S, band && S, band && S > 1);
+  const Bufs B = solve_bufs(h);
+  const std::vector<int> round = round_launches(h->band_mode == BAND_FACTOR, B.nest.S > 0, B.nest.S > 1);
   const int per = (int)round.size();
   for (int i = 0; i < per * kRounds && err == hipSuccess; ++i)
-    err = launch_rotation(h->D, h->B, i & 1, round[(size_t)(i % per)], h->stream, mixed);
+    err = launch_rotation(h->D, B, i & 1, round[(size_t)(i % per)], h->stream, mixed);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(h->stream, &g);
   if (err != hipSuccess) return fail(FLR_ERR_DEVICE, std::string("capture launch: ") + hipGetErrorString(err));
@@ -236,9 +266,16 @@ struct SolveRun {
   std::chrono::steady_clock::time_point t0;
 };
 
+// Preconditioner that AUTO stands for (an flr_precond value).
+int auto_preconditioner(flr_problem h, double l1) {
+  return !(l1 > 0.0) ? FLR_PRECOND_JACOBI : h->band_w ? FLR_PRECOND_BAND : FLR_PRECOND_TRIDIAG;
+}
+
 // Parameters, warm start and initial state of a solve (solve_begin adds the
 // captured rotation; the ragged batch captures grouped launches instead).
-flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, SolveRun& run) {
+// may_nest: whether the nested inverses' memory may be taken.
+flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, SolveRun& run,
+                         bool may_nest) {
   run.t0 = std::chrono::steady_clock::now();
   run.h = h;
   flr_solve_opts dflt;
@@ -258,14 +295,14 @@ flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const 
   P.max_cg = o->max_cg > 0 ? o->max_cg : (int32_t)std::min<int64_t>(D.p, INT32_MAX);
   int pre = o->preconditioner;
   if (pre < FLR_PRECOND_AUTO || pre > FLR_PRECOND_BAND) return fail(FLR_ERR_INVALID_ARG, "unknown preconditioner");
-  if (pre == FLR_PRECOND_AUTO)
-    pre = !(l1 > 0.0) ? FLR_PRECOND_JACOBI : h->band_w ? FLR_PRECOND_BAND : FLR_PRECOND_TRIDIAG;
+  if (pre == FLR_PRECOND_AUTO) pre = auto_preconditioner(h, l1);
   if ((pre == FLR_PRECOND_TRIDIAG || pre == FLR_PRECOND_BAND) && !(l1 > 0.0))
     return fail(FLR_ERR_INVALID_ARG, "the tridiagonal and banded preconditioners need lambda1 > 0 (M is singular otherwise)");
   if (pre == FLR_PRECOND_BAND && !h->band_w)
     return fail(FLR_ERR_INVALID_ARG, "banded preconditioner: the edge set has bandwidth < 2 or its band is too wide");
   P.jacobi = pre == FLR_PRECOND_JACOBI ? 1 : 0;
   P.band = pre == FLR_PRECOND_BAND ? h->band_w : 0;
+  h->band_mode = !P.band ? BAND_NONE : may_nest && nest_ready(h) ? BAND_NEST : BAND_FACTOR;
   P.mixed = o->precision == FLR_PREC_MIXED_FP32 ? 1 : 0;
   HIP_OR_FAIL(hipMemcpyAsync(h->d_prm, h->h_prm, sizeof(Params), hipMemcpyHostToDevice, h->stream));
 
@@ -289,21 +326,21 @@ flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const 
   // refreshes (mixed precision: each follows at least one PCG step) and its
   // boundary (with nested inverses, a factorization of at least one stage per
   // round); one graph launch holds kRounds rotations
-  run.max_launches = ((int64_t)P.max_iter * (2 * (int64_t)P.max_cg + 2 + h->B.nest.stages) + 2) / kRounds + 4;
+  run.max_launches = ((int64_t)P.max_iter * (2 * (int64_t)P.max_cg + 2 + h->nest.stages) + 2) / kRounds + 4;
   run.launched = 0;
   run.in_flight = 0;
   run.done = false;
   return FLR_OK;
 }
 
-flr_status solve_begin(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, SolveRun& run) {
-  flr_status st = solve_prepare(h, l1, l2, tol, o, run);
+flr_status solve_begin(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, SolveRun& run,
+                       bool may_nest) {
+  flr_status st = solve_prepare(h, l1, l2, tol, o, run, may_nest);
   if (st != FLR_OK) return st;
   const bool mixed = h->h_prm->mixed != 0;
-  const bool band = h->h_prm->band != 0;
-  st = build_graph(h, mixed, band);
+  st = build_graph(h, mixed);
   if (st != FLR_OK) return st;
-  run.gexec = h->gexec[mixed][band];
+  run.gexec = h->gexec[mixed][h->band_mode];
   return FLR_OK;
 }
 
@@ -364,14 +401,14 @@ flr_status solve_end(SolveRun& run, double* beta_out, flr_result* res) {
 
 // One solve on the problem's stream; beta_out host or device (or nullptr).
 flr_status run_solve(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, double* beta_out,
-                     flr_result* res) {
+                     flr_result* res, bool may_nest = true) {
   if (o && o->method != FLR_METHOD_PCG) {
     if (o->method != FLR_METHOD_CHOLESKY) return fail(FLR_ERR_INVALID_ARG, "unknown method");
     if (!(o->eps >= 0.0) || o->max_iter < 0) return fail(FLR_ERR_INVALID_ARG, "options out of range");
     return dense_run(h, l1, l2, tol, o, beta_out, res);
   }
   SolveRun run;
-  flr_status st = solve_begin(h, l1, l2, tol, o, run);
+  flr_status st = solve_begin(h, l1, l2, tol, o, run, may_nest);
   if (st != FLR_OK) return st;
   // FLR_PROGRESS=1: a line on stderr every few seconds from the polling loop
   const char* prog_env = std::getenv("FLR_PROGRESS");
@@ -439,16 +476,16 @@ flr_status batch_run(const flr_problem* hs, int32_t count, std::vector<SolveRun>
         if (h->D.dtype != dt || (h->h_prm->mixed != 0) != (mx != 0)) continue;
         GroupEntry e{};
         e.D = h->D;
-        e.B = h->B;
+        e.B = solve_bufs(h);
         e.wg_a = g.wa;
         e.wg_b = g.wb;
         e.wg_c = g.wc;
         e.wg_k = g.wk;
-        e.band = band_mode(h);
-        e.wgs_k = e.band == BAND_NEST ? h->B.nest.wgs : 1;
+        e.band = h->band_mode;
+        e.wgs_k = e.band == BAND_NEST ? e.B.nest.wgs : 1;
         g.wk += e.wgs_k;
         g.modes[e.band] = true;
-        g.tops = g.tops || (e.band == BAND_NEST && h->B.nest.S > 1);
+        g.tops = g.tops || e.B.nest.S > 1;
         g.wa += h->D.cb1 * h->D.rb1;
         g.wb += h->D.gridB;
         g.wc += h->D.nblk;
@@ -515,15 +552,48 @@ flr_status batch_run(const flr_problem* hs, int32_t count, std::vector<SolveRun>
 
 namespace flr {
 flr_status solve_locked(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, double* beta_out,
-                        flr_result* res) {
+                        flr_result* res, bool may_nest) {
   flr_status v = validate_lambdas(l1, l2, tol);
   if (v != FLR_OK) return v;
   if (hipSetDevice(h->ctx->device) != hipSuccess) return fail(FLR_ERR_DEVICE, "hipSetDevice failed");
-  return run_solve(h, l1, l2, tol, o, beta_out, res);
+  if (!may_nest) nest_release(h);
+  return run_solve(h, l1, l2, tol, o, beta_out, res, may_nest);
+}
+// Bytes that a budget has to hold for this solve.  The nested inverses are asked
+// for where the budget can hold them at all; else *may_nest is false, the solve
+// applies the band factor that the handle holds anyway, and gives up the inverses'
+// memory if an earlier one took it.  The answer depends on the handle, the solve
+// and the budget, not on what else runs, and so does the result.
+size_t solve_bytes(flr_problem h, double l1, const flr_solve_opts* o, size_t budget, bool* may_nest) {
+  const int pre = o && o->preconditioner != FLR_PRECOND_AUTO ? o->preconditioner : auto_preconditioner(h, l1);
+  const bool wanted = h->nest.S && pre == FLR_PRECOND_BAND && !(o && o->method != FLR_METHOD_PCG);
+  const size_t least = h->footprint, full = least + h->nest_bytes;
+  if (!wanted && !h->nest_held) {
+    *may_nest = true;
+    return least;
+  }
+  *may_nest = full <= budget;
+  return *may_nest ? full : least;
+}
+// Gives the nested inverses' memory back (the next solve that applies them takes it
+// again); true if there was any.  The caller holds the handle's mutex.
+bool nest_release(flr_problem h) {
+  if (!h->nest_mem) return false;
+  (void)hipStreamSynchronize(h->stream);
+  for (int a = 0; a < 2; ++a) {
+    if (h->gexec[a][BAND_NEST]) (void)hipGraphExecDestroy(h->gexec[a][BAND_NEST]);
+    if (h->graph[a][BAND_NEST]) (void)hipGraphDestroy(h->graph[a][BAND_NEST]);
+    h->gexec[a][BAND_NEST] = nullptr;
+    h->graph[a][BAND_NEST] = nullptr;
+  }
+  (void)hipFree(h->nest_mem);
+  h->nest_mem = nullptr;
+  h->nest_held = false;
+  nest_carve(h->nest, nullptr);
+  return true;
 }
 std::mutex& problem_mutex(flr_problem h) { return h->busy; }
 bool is_device_pointer(const void* p) { return is_device_ptr(p); }
-size_t problem_footprint(flr_problem h) { return h->footprint; }
 int problem_device(flr_problem h) { return h->ctx->device; }
 void set_last_error(const std::string& s) { g_last_error = s; }
 }  // namespace flr
@@ -587,8 +657,9 @@ static void problem_free(flr_problem h) {
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   flr::grid_free(h);
   flr::dense_free(h);
+  flr::nest_release(h);
   for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < 3; ++b) {
       if (h->gexec[a][b]) (void)hipGraphExecDestroy(h->gexec[a][b]);
       if (h->graph[a][b]) (void)hipGraphDestroy(h->graph[a][b]);
     }
@@ -720,21 +791,11 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
     for (auto& e : ev) bw = std::max(bw, e.second - e.first);
     const int64_t W = bw + 1;
     if (bw >= 2 && W <= kBandMaxW && (double)p * (double)W * 8.0 <= 4.0 * (1 << 30)) {
-      B.nest = nest_plan(p, bw);
-      if (B.nest.S) {
-        const hipError_t e = nest_alloc(h, B.nest);
-        if (e == hipErrorOutOfMemory) {
-          (void)hipGetLastError();
-          B.nest = Nest{};  // the band factor (q = 224 lattice: 0.18 GB against 1.3) may still fit
-        } else {
-          CK(e);
-        }
-      }
-      if (!B.nest.S) {
-        CK(dalloc(h, &B.Lb, (size_t)p * (size_t)W));
-        CK(dalloc(h, &B.LbT, (size_t)p * (size_t)W));
-        CK(dalloc(h, &B.invdb, (size_t)D.p_pad));
-      }
+      h->nest = nest_plan(p, bw);
+      if (h->nest.S) h->nest_bytes = nest_carve(h->nest, nullptr);
+      CK(dalloc(h, &B.Lb, (size_t)p * (size_t)W));
+      CK(dalloc(h, &B.LbT, (size_t)p * (size_t)W));
+      CK(dalloc(h, &B.invdb, (size_t)D.p_pad));
       CK(dalloc(h, &B.btmp, (size_t)D.p_pad));
       h->band_w = (int)W;
     }
@@ -798,7 +859,7 @@ void flr_destroy(flr_problem h) { problem_free(h); }
 
 flr_status flr_problem_footprint(flr_problem h, size_t* bytes) {
   if (!h || !bytes) return fail(FLR_ERR_INVALID_ARG, "NULL argument");
-  *bytes = h->footprint;
+  *bytes = h->footprint + (h->nest_held ? h->nest_bytes : 0);
   return FLR_OK;
 }
 int64_t flr_problem_n(flr_problem h) { return h ? h->D.n : -1; }
@@ -850,7 +911,7 @@ flr_status flr_solve_batch(const flr_problem* hs, int32_t count, const double* l
     return fail(FLR_ERR_INVALID_ARG, "flr_solve_batch runs Algorithm 2 (PCG) only");
   std::vector<SolveRun> runs((size_t)count);
   for (int32_t i = 0; i < count; ++i) {
-    flr_status st = solve_prepare(hs[i], l1[i], l2[i], tol, opts, runs[(size_t)i]);
+    flr_status st = solve_prepare(hs[i], l1[i], l2[i], tol, opts, runs[(size_t)i], true);
     if (st != FLR_OK) {
       for (int32_t k = 0; k < i; ++k) (void)hipStreamSynchronize(hs[k]->stream);
       return st;
@@ -931,6 +992,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   std::unique_lock<std::mutex> lk(h->busy, std::try_to_lock);
   if (!lk.owns_lock()) return fail(FLR_ERR_BUSY, "problem handle in use by another thread");
   HIP_OR_FAIL(hipSetDevice(h->ctx->device));
+  const Bufs B = solve_bufs(h);
   State cg{};
   cg.phase = PH_CG;
   cg.first_cg = 1;
@@ -944,7 +1006,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   HIP_OR_FAIL(hipEventCreate(&e2));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 0, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, B, 0, 0, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
@@ -952,14 +1014,14 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   float ms_a = 0.f;
   // re-time A from its own start event
   HIP_OR_FAIL(hipEventRecord(e0, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 0, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, B, 0, 0, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   HIP_OR_FAIL(hipEventElapsedTime(&ms_a, e0, e1));
   float ms_b = 0.f;
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 1, 1, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, B, 1, 1, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e2, h->stream));
   HIP_OR_FAIL(hipStreamSynchronize(h->stream));
   HIP_OR_FAIL(hipEventElapsedTime(&ms_b, e1, e2));
@@ -973,7 +1035,7 @@ flr_status flr_profile_kernels(flr_problem h, int32_t reps, double* avg_us) {
   HIP_OR_FAIL(hipMemcpyAsync(h->B.st, hs, 2 * sizeof(State), hipMemcpyHostToDevice, h->stream));
   float ms_c = 0.f;
   HIP_OR_FAIL(hipEventRecord(e1, h->stream));
-  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, h->B, 0, 2, h->stream, false));
+  for (int i = 0; i < reps; ++i) HIP_OR_FAIL(launch_rotation(h->D, B, 0, 2, h->stream, false));
   HIP_OR_FAIL(hipEventRecord(e2, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.x, save, vb, hipMemcpyDeviceToDevice, h->stream));
   HIP_OR_FAIL(hipMemcpyAsync(h->B.r, save + h->D.p_pad, vb, hipMemcpyDeviceToDevice, h->stream));

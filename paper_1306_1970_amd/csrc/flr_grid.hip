@@ -689,8 +689,12 @@ static flr_status grid_prepare_once(flr_problem h, int B, bool band);
 
 static flr_status grid_prepare(flr_problem h, int B, bool band) {
   if (h->grid && h->grid->cap >= B && (h->grid->band || !band)) return FLR_OK;
-  grid_free(h);
-  const flr_status st = grid_prepare_once(h, B, band);
+  flr_status st;
+  do {  // a second time without the memory that a single solve's inverses hold
+    if (h->grid) (void)hipStreamSynchronize(h->stream);
+    grid_free(h);
+    st = grid_prepare_once(h, B, band);
+  } while (st == FLR_ERR_OUT_OF_MEMORY && nest_release(h));
   if (st != FLR_OK) {
     (void)hipStreamSynchronize(h->stream);
     grid_free(h);

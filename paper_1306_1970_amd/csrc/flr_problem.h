@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -41,11 +42,16 @@ struct flr_problem_s {
   Params* h_prm = nullptr;  // pinned
   State* h_state = nullptr; // pinned, 2 slots
   hipEvent_t ev[2] = {nullptr, nullptr};
-  hipGraph_t graph[2][2] = {};         // [mixed][banded]
-  hipGraphExec_t gexec[2][2] = {};
+  hipGraph_t graph[2][3] = {};         // [mixed][flr::BandMode]
+  hipGraphExec_t gexec[2][3] = {};
   int band_w = 0;                       // bandwidth + 1 of E when the banded factor is allocated, else 0
+  int band_mode = 0;                    // flr::BandMode of the current (last) solve
+  flr::Nest nest{};                     // plan of the nested inverses; its buffers from the first solve that uses them
+  size_t nest_bytes = 0;                // what they take
+  void* nest_mem = nullptr;             // one block, null: not held
+  std::atomic<bool> nest_held{false};   // nest_mem, for threads that do not hold `busy`
   std::vector<void*> allocs;
-  size_t footprint = 0;
+  size_t footprint = 0;                 // without nest_mem
   bool has_solution = false;
   std::mutex busy;
   int64_t edges_m = 0;
@@ -58,6 +64,7 @@ namespace flr {
 void set_last_error(const std::string& s);
 void grid_free(flr_problem h);
 void dense_free(flr_problem h);
+bool nest_release(flr_problem h);
 flr_status dense_run(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, double* beta_out,
                      flr_result* res);
 flr_status dense_profile(flr_problem h, double l1, double l2, int32_t reps, double* avg_us);

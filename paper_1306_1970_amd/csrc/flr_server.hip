@@ -24,9 +24,9 @@
 
 namespace flr {
 flr_status solve_locked(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, double* beta_out,
-                        flr_result* res);
+                        flr_result* res, bool may_nest);
+size_t solve_bytes(flr_problem h, double l1, const flr_solve_opts* o, size_t budget, bool* may_nest);
 std::mutex& problem_mutex(flr_problem h);
-size_t problem_footprint(flr_problem h);
 int problem_device(flr_problem h);
 void set_last_error(const std::string& s);
 }  // namespace flr
@@ -40,6 +40,7 @@ struct Request {
   double l1 = 0, l2 = 0, tol = 0;
   flr_solve_opts opts{};
   bool has_opts = false;
+  bool may_nest = true;
   size_t bytes = 0;
   std::chrono::steady_clock::time_point t_submit;
 };
@@ -101,7 +102,8 @@ static void worker_loop(flr_server s) {
     d.beta.resize((size_t)flr_problem_p(rq.h));
     {
       std::lock_guard<std::mutex> pl(flr::problem_mutex(rq.h));
-      d.st = flr::solve_locked(rq.h, rq.l1, rq.l2, rq.tol, rq.has_opts ? &rq.opts : nullptr, d.beta.data(), &d.res);
+      d.st = flr::solve_locked(rq.h, rq.l1, rq.l2, rq.tol, rq.has_opts ? &rq.opts : nullptr, d.beta.data(), &d.res,
+                               rq.may_nest);
     }
     d.res.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - rq.t_submit).count();
     {
@@ -152,7 +154,7 @@ flr_status flr_server_submit(flr_server s, flr_problem h, double l1, double l2, 
     rq.has_opts = true;
     rq.opts.warm_start = nullptr;  // a caller buffer may not outlive the call; use_last still applies
   }
-  rq.bytes = flr::problem_footprint(h);
+  rq.bytes = flr::solve_bytes(h, l1, opts, s->budget, &rq.may_nest);
   if (rq.bytes > s->budget) {
     flr::set_last_error("flr_server_submit: problem footprint exceeds the server budget");
     return FLR_ERR_BUSY;

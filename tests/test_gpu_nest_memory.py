@@ -1,0 +1,92 @@
+"""The memory of the nested dense inverses: taken by the first solve that applies
+them and by no other, never a reason to refuse a request or a solve, and given
+back when a server's budget cannot hold it.  Without it a solve applies the
+banded factor: same iterates to the FP64 bar of the parity tests (1e-8 of
+max |beta|)."""
+import numpy as np
+import pytest
+
+import flrgen
+
+pytestmark = pytest.mark.gpu
+OPTS = dict(inner_tol=1e-12, max_iter=2)
+
+
+@pytest.fixture(scope="module")
+def flr():
+    import torch
+
+    assert torch.cuda.is_available()
+    import paper_1306_1970_amd as m
+
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(flr):
+    c = flr.Context(0)
+    yield c
+    c.close()
+
+
+def _close(a, b):
+    err = np.max(np.abs(a - b)) / np.max(np.abs(b))
+    print("  difference %.2g" % err, flush=True)
+    assert err <= 1e-8
+
+
+def _served(flr, ctx, prob, budget):
+    srv = flr.flr_server_create(ctx.h, budget, 1)
+    t = flr.flr_server_submit(srv, prob.h, 0.3, 0.7, 1e-14, flr.default_opts(**OPTS))
+    beta = np.zeros(prob.p)
+    st, res = flr.flr_server_poll(srv, t, True, beta)
+    flr.flr_server_destroy(srv)
+    assert st == flr.FLR_ERR_MAX_ITER  # both MM steps ran
+    return beta
+
+
+@pytest.mark.parametrize("q", [20, 40])  # one segment; segments and separators
+def test_budget_of_the_banded_factor_is_enough(flr, ctx, q):
+    y = np.random.default_rng(q).standard_normal(q * q)
+    prob = flr.Problem.flsa(ctx, y, flrgen.lattice_edges(q))
+    base = prob.footprint
+    prob.solve(0.3, 0.7, tol=1e-14, preconditioner=flr.FLR_PRECOND_TRIDIAG, max_iter=1)
+    assert prob.footprint == base  # another preconditioner takes none of it
+    print("q=%d: budget %d" % (q, base), flush=True)
+    small = _served(flr, ctx, prob, base)
+    assert prob.footprint == base
+    solo = prob.solve(0.3, 0.7, tol=1e-14, **OPTS)
+    full = prob.footprint
+    assert full > base
+    _close(small, solo.beta)
+    assert np.array_equal(_served(flr, ctx, prob, full), solo.beta)
+    assert np.array_equal(_served(flr, ctx, prob, base), small)  # accepted as before, and the memory given back
+    assert prob.footprint == base
+    again = prob.solve(0.3, 0.7, tol=1e-14, **OPTS)  # taken again, rotation captured again
+    assert prob.footprint == full
+    assert np.array_equal(again.beta, solo.beta)
+    prob.close()
+
+
+def test_solve_where_the_memory_is_not_free(flr, ctx):
+    import torch
+
+    p, bw = 200000, 2
+    rng = np.random.default_rng(3)
+    y = np.repeat(rng.uniform(-2, 2, p // 8), 8) + 0.3 * rng.standard_normal(p)
+    j = np.arange(p - 1)
+    e = np.concatenate([np.stack([j, j + 1], 1), np.stack([np.arange(p - bw), np.arange(bw, p)], 1)])
+    prob = flr.Problem.flsa(ctx, y, e.astype(np.int64))
+    base = prob.footprint
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    held = torch.empty(free - 2500 * 2 ** 20, dtype=torch.uint8, device="cuda:0")
+    print("p=%d bw=%d: %d MiB left free" % (p, bw, torch.cuda.mem_get_info()[0] >> 20), flush=True)
+    tight = prob.solve(0.3, 0.7, tol=1e-14, **OPTS)
+    assert prob.footprint == base
+    del held
+    torch.cuda.empty_cache()
+    s = prob.solve(0.3, 0.7, tol=1e-14, **OPTS)
+    assert prob.footprint > base + 2 ** 29
+    _close(tight.beta, s.beta)
+    prob.close()
