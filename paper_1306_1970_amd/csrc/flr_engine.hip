@@ -271,6 +271,20 @@ int auto_preconditioner(flr_problem h, double l1) {
   return !(l1 > 0.0) ? FLR_PRECOND_JACOBI : h->band_w ? FLR_PRECOND_BAND : FLR_PRECOND_TRIDIAG;
 }
 
+// Whether an explicit inverse of M is accurate enough to precondition with: its
+// rounding, 2^-53 ||M^-1||, has to stay below its least eigenvalue 1 / ||M||, or the
+// stiff directions (couplings near lambda2 / eps) are lost.  kappa bounds the condition
+// number with the initial iterate's size for |b|.  PCG steps against the band factor's,
+// whose triangular solves do not suffer so: all pairs of 60 the same at kappa = 1e10,
+// 1.3 x at 1e14 (where a step is still 1.6 x faster), 2 x at 1e16, 60 x and numerical
+// failures at 1e18; lattices the same at 1e16, 2 x at 1e18.  eps = 1e-8, |b| = 2:
+// lattices down to lambda1 = 2e-5 lambda2.
+bool nest_accurate(flr_problem h, double l1, double l2, const flr_solve_opts* o) {
+  const double eps = o && o->eps > 0.0 ? o->eps : 1e-8;
+  const double kappa = (l1 + 2.0 * (double)h->max_deg * l2) / eps * ((h->beta0 + eps) / l1);
+  return kappa <= 0x1p46;
+}
+
 // Parameters, warm start and initial state of a solve (solve_begin adds the
 // captured rotation; the ragged batch captures grouped launches instead).
 // may_nest: whether the nested inverses' memory may be taken.
@@ -302,7 +316,9 @@ flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const 
     return fail(FLR_ERR_INVALID_ARG, "banded preconditioner: the edge set has bandwidth < 2 or its band is too wide");
   P.jacobi = pre == FLR_PRECOND_JACOBI ? 1 : 0;
   P.band = pre == FLR_PRECOND_BAND ? h->band_w : 0;
-  h->band_mode = !P.band ? BAND_NONE : may_nest && nest_ready(h) ? BAND_NEST : BAND_FACTOR;
+  h->band_mode = !P.band                                                         ? BAND_NONE
+                 : may_nest && nest_accurate(h, l1, l2, o) && nest_ready(h) ? BAND_NEST
+                                                                                 : BAND_FACTOR;
   P.mixed = o->precision == FLR_PREC_MIXED_FP32 ? 1 : 0;
   HIP_OR_FAIL(hipMemcpyAsync(h->d_prm, h->h_prm, sizeof(Params), hipMemcpyHostToDevice, h->stream));
 
@@ -564,9 +580,10 @@ flr_status solve_locked(flr_problem h, double l1, double l2, double tol, const f
 // applies the band factor that the handle holds anyway, and gives up the inverses'
 // memory if an earlier one took it.  The answer depends on the handle, the solve
 // and the budget, not on what else runs, and so does the result.
-size_t solve_bytes(flr_problem h, double l1, const flr_solve_opts* o, size_t budget, bool* may_nest) {
+size_t solve_bytes(flr_problem h, double l1, double l2, const flr_solve_opts* o, size_t budget, bool* may_nest) {
   const int pre = o && o->preconditioner != FLR_PRECOND_AUTO ? o->preconditioner : auto_preconditioner(h, l1);
-  const bool wanted = h->nest.S && pre == FLR_PRECOND_BAND && !(o && o->method != FLR_METHOD_PCG);
+  const bool wanted = h->nest.S && pre == FLR_PRECOND_BAND && !(o && o->method != FLR_METHOD_PCG) &&
+                      nest_accurate(h, l1, l2, o);
   const size_t least = h->footprint, full = least + h->nest_bytes;
   if (!wanted && !h->nest_held) {
     *may_nest = true;
@@ -816,7 +833,7 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   CK(hipMemcpyAsync(cl, col.data(), col.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
   CK(hipMemcpyAsync(pp, prevpos.data(), prevpos.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
   int hflag = 0;
-  std::vector<double> hc((size_t)D.p);
+  std::vector<double> hc((size_t)D.p), hs((size_t)D.p, 1.0);
   if (!flsa) {
     CK(launch_check_finite(Xd, x_dtype, (int64_t)n * D.ldx, flag, h->stream));
     cpart = B.qpart;
@@ -824,12 +841,12 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
     CK(launch_setup(D, Xd, yd, cpart, spart, c, s, h->stream));
     CK(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     CK(hipMemcpyAsync(hc.data(), c, (size_t)D.p * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    CK(hipMemcpyAsync(hs.data(), s, (size_t)D.p * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     CK(hipStreamSynchronize(h->stream));
   } else {
     // X = I: c = X^T y = y, ||X_j||^2 = 1 (the padding keeps zeros from dalloc)
-    std::vector<double> ones((size_t)D.p, 1.0);
     CK(hipMemcpyAsync(c, y, (size_t)D.p * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    CK(hipMemcpyAsync(s, ones.data(), (size_t)D.p * sizeof(double), hipMemcpyHostToDevice, h->stream));
+    CK(hipMemcpyAsync(s, hs.data(), (size_t)D.p * sizeof(double), hipMemcpyHostToDevice, h->stream));
     CK(hipStreamSynchronize(h->stream));
     std::copy(y, y + D.p, hc.begin());
   }
@@ -837,6 +854,9 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   double cn = 0.0;
   for (double v : hc) cn += v * v;
   h->cnorm = std::sqrt(cn);
+  for (size_t j = 0; j < hc.size(); ++j)
+    if (hs[j] > 0.0) h->beta0 = std::max(h->beta0, std::fabs(hc[j]) / hs[j]);
+  for (size_t j = 0; j < (size_t)p; ++j) h->max_deg = std::max<int64_t>(h->max_deg, deg[j + 1]);
 #undef CK
   *out = h;
   return FLR_OK;

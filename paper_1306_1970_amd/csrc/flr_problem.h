@@ -37,6 +37,8 @@ struct flr_problem_s {
   int64_t m = 0;
   int64_t nnz = 0;
   double cnorm = 0.0;
+  double beta0 = 0.0;   // largest |b_j| of the initial iterate
+  int64_t max_deg = 0;  // edges of the busiest index
   hipStream_t stream = nullptr;
   Params* d_prm = nullptr;
   Params* h_prm = nullptr;  // pinned

@@ -25,7 +25,7 @@
 namespace flr {
 flr_status solve_locked(flr_problem h, double l1, double l2, double tol, const flr_solve_opts* o, double* beta_out,
                         flr_result* res, bool may_nest);
-size_t solve_bytes(flr_problem h, double l1, const flr_solve_opts* o, size_t budget, bool* may_nest);
+size_t solve_bytes(flr_problem h, double l1, double l2, const flr_solve_opts* o, size_t budget, bool* may_nest);
 std::mutex& problem_mutex(flr_problem h);
 int problem_device(flr_problem h);
 void set_last_error(const std::string& s);
@@ -154,7 +154,7 @@ flr_status flr_server_submit(flr_server s, flr_problem h, double l1, double l2, 
     rq.has_opts = true;
     rq.opts.warm_start = nullptr;  // a caller buffer may not outlive the call; use_last still applies
   }
-  rq.bytes = flr::solve_bytes(h, l1, opts, s->budget, &rq.may_nest);
+  rq.bytes = flr::solve_bytes(h, l1, l2, opts, s->budget, &rq.may_nest);
   if (rq.bytes > s->budget) {
     flr::set_last_error("flr_server_submit: problem footprint exceeds the server budget");
     return FLR_ERR_BUSY;

@@ -65,3 +65,62 @@ def test_chain(flr, ctx, p, l1):
     prob.close()
     assert s.cg_iters < 20 * p
     _check(y, s, ref, qnorm)
+
+
+def _pcg_steps(y, e, bw, l1, eps, steps):
+    """PCG steps of `steps` MM iterations on the CPU, M^-1 from scipy's banded Cholesky solve."""
+    p, b, cg = y.size, y.copy(), 0
+    j, k = e[:, 0], e[:, 1]
+    nc = np.linalg.norm(y)
+    for _ in range(steps):
+        a = l1 / (np.abs(b) + eps)
+        w = L2 / (np.abs(b[j] - b[k]) + eps)
+        ab = np.zeros((bw + 1, p))
+        ab[bw - (k - j), k] = -w
+        ab[bw] = a + np.bincount(j, w, p) + np.bincount(k, w, p)
+
+        def m(v):
+            d = w * (v[j] - v[k])
+            return a * v + np.bincount(j, d, p) - np.bincount(k, d, p)
+
+        r = y - (b + m(b))
+        z = solveh_banded(ab, r)
+        q, rz = z.copy(), r @ z
+        while True:
+            v = q + m(q)
+            nu = rz / (q @ v)
+            b = b + nu * q
+            r -= nu * v
+            cg += 1
+            if not np.linalg.norm(r) / nc > INNER:
+                break
+            z = solveh_banded(ab, r)
+            rzn = r @ z
+            q = z + rzn / rz * q
+            rz = rzn
+    return cg
+
+
+@pytest.mark.parametrize("graph,p,l1,eps", [("lattice", 100, 1e-10, 1e-8), ("lattice", 100, 1e-8, 1e-10),
+                                            ("lattice", 1600, 1e-10, 1e-8), ("allpairs", 60, 1e-5, 1e-8),
+                                            ("allpairs", 60, 1e-5, 1e-11)])
+def test_banded(flr, ctx, graph, p, l1, eps):
+    # an explicit inverse of M rounds its small eigenvalues away here (up to 60 times the steps, or a numerical
+    # failure), so the solve keeps the band factor.  The steps stay within a quarter of the CPU's: both
+    # factorizations round, by different amounts.
+    rng = np.random.default_rng(p)
+    y = np.repeat(rng.uniform(-2, 2, p // 12 + 1), 12)[:p] + 0.1 * rng.standard_normal(p)
+    e = flrgen.lattice_edges(int(p ** 0.5)) if graph == "lattice" else np.stack(np.triu_indices(p, 1), 1)
+    e = np.asarray(e, dtype=np.int64)
+    print("%s p=%d lambda1=%g eps=%g" % (graph, p, l1, eps), flush=True)
+    cg = _pcg_steps(y, e, int((e[:, 1] - e[:, 0]).max()), l1, eps, 4)
+    prob = flr.Problem.flsa(ctx, y, e)
+    base = prob.footprint
+    s = prob.solve(l1, L2, tol=1e-14, inner_tol=INNER, max_iter=4, eps=eps, max_cg=2000)
+    print("  status %d, %d PCG steps (CPU %d)" % (s.status, s.cg_iters, cg), flush=True)
+    assert s.status == flr.FLR_ERR_MAX_ITER  # all four MM steps ran
+    assert s.cg_iters <= cg + max(5, cg // 4)
+    assert prob.footprint == base
+    prob.solve(0.3, L2, tol=1e-6)
+    assert prob.footprint > base  # and where M is well conditioned the inverses are used
+    prob.close()
