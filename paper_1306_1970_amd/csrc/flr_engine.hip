@@ -117,19 +117,21 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
 // next pivot block) or its tiles at 3.4 us of matrix-core time per CU.  The
 // minimum is flat: twice the stage times (measured, 24 to 31) move S by one or
 // two.  Small orders stay whole (S = 1 up to p of about 1100); 100 x 100 gives
-// S = 15, 128 x 128 S = 19.  S = 0, the band factor in
+// S = 15, 128 x 128 S = 19, p = 2 10^5 with bw = 2 S = 1184.  The separators'
+// right-hand side has to fit the LDS, which ends S; the least time is near the least
+// memory too (p = 2 10^5, bw = 2: 1.05 GB, with S = 128 3.1).  S = 0, the band factor in
 // one workgroup instead, where the matrices pass 4 GB (the band factor's own
 // limit) or a segment the LDS.
 Nest nest_plan(int64_t p, int64_t bw) {
   Nest best{};
   double best_cost = 0.0;
-  for (int64_t S = 1; S <= 128; ++S) {
+  for (int64_t S = 1; (S - 1) * bw <= kNestLds - kNT; ++S) {
     const int64_t m = S == 1 ? p : (p - (S - 1) * bw + S - 1) / S;
     if (S > 1 && m < bw) break;
     if (p - (S - 1) * (m + bw) < 1) continue;
     const int64_t nt = (S - 1) * bw, mt = (m + kTile - 1) / kTile, bt = S == 1 ? 0 : (2 * bw + kTile - 1) / kTile;
     const int64_t tt = (nt + kTile - 1) / kTile, N = kTile * (mt + bt), ntp = kTile * tt;
-    if (m > kNestLds - kNT || nt > kNestLds - kNT) continue;
+    if (m > kNestLds - kNT) continue;
     const int64_t pans = std::max(S * (mt + bt), tt);
     const double mem = 8.0 * ((double)S * N * N + (double)ntp * ntp + 2.0 * (pans + S) * kTE);
     if (mem > 4.0 * (1 << 30)) continue;

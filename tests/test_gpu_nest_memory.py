@@ -87,6 +87,6 @@ def test_solve_where_the_memory_is_not_free(flr, ctx):
     del held
     torch.cuda.empty_cache()
     s = prob.solve(0.3, 0.7, tol=1e-14, **OPTS)
-    assert prob.footprint > base + 2 ** 29
+    assert base + 2 ** 29 < prob.footprint < base + 3 * 2 ** 29  # 1184 segments; cut into 128 they took 3.1 GB
     _close(tight.beta, s.beta)
     prob.close()
