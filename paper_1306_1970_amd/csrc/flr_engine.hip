@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <initializer_list>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -65,6 +66,20 @@ hipError_t dalloc(flr_problem h, T** p, size_t count) {
 
 int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
+// 512 workgroups per GEMV launch (two per CU): measured best on the
+// n = 1000, p = 10^4 f32 workload (A 9.1 us, B 10.8 us per launch, and
+// fewer column-panel partials for the block kernel to sum) over 256..2048
+constexpr int kTargetWg = 512;
+
+// Rows per row panel of B: what its target of workgroups takes, `least` or more.
+int64_t panel_rows_b(int64_t n, int64_t cb2, int64_t least) {
+  const char* tb = getenv("FLR_TARGET_WG_B");
+  const int64_t target = tb ? atoi(tb) : kTargetWg;
+  int64_t rb2 = std::max<int64_t>(1, (target + cb2 - 1) / cb2);
+  rb2 = std::min<int64_t>(rb2, std::max<int64_t>(1, n / least));
+  return std::min<int64_t>((n + rb2 - 1) / rb2, kMaxR2);
+}
+
 Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
   Dims D{};
   D.n = n;
@@ -78,26 +93,17 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
   D.ldx = D.p_pad;
   D.cb1 = (int32_t)(D.p_pad / D.c1);
   const char* ta = getenv("FLR_TARGET_WG_A");
-  const char* tb = getenv("FLR_TARGET_WG_B");
-  // 512 workgroups per GEMV launch (two per CU): measured best on the
-  // n = 1000, p = 10^4 f32 workload (A 9.1 us, B 10.8 us per launch, and
-  // fewer column-panel partials for the block kernel to sum) over 256..2048
-  const int target = ta ? atoi(ta) : 512;
-  const int target_b = tb ? atoi(tb) : 512;
+  const int target = ta ? atoi(ta) : kTargetWg;
   int64_t rb1 = std::max<int64_t>(1, (target + D.cb1 - 1) / D.cb1);
   rb1 = std::min<int64_t>(rb1, std::max<int64_t>(1, n / 4));
   D.r1 = (int32_t)((n + rb1 - 1) / rb1);
   D.rb1 = (int32_t)((n + D.r1 - 1) / D.r1);
   D.cb2 = (int32_t)(D.p_pad / D.c2);
-  int64_t rb2 = std::max<int64_t>(1, (target_b + D.cb2 - 1) / D.cb2);
   // at least 32 rows per row panel (one batch of eight rows in flight per
   // wave): a finer split only adds partials for the block kernel to sum
   // (n = 1000, p = 200 f64: 128 panels 45 us per PCG step, 31 panels 19 us)
-  rb2 = std::min<int64_t>(rb2, std::max<int64_t>(1, n / 32));
-  int64_t r2 = (n + rb2 - 1) / rb2;
-  if (r2 > kMaxR2) r2 = kMaxR2;
-  D.r2 = (int32_t)r2;
-  D.rb2 = (int32_t)((n + r2 - 1) / r2);
+  D.r2 = (int32_t)panel_rows_b(n, D.cb2, 32);
+  D.rb2 = (int32_t)((n + D.r2 - 1) / D.r2);
   if (flsa) {  // X = I: one row panel per column panel, nothing streamed
     D.rb1 = 1;
     D.r1 = (int32_t)std::min<int64_t>(n, INT32_MAX);
@@ -797,7 +803,13 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   CK(dalloc(h, &B.sig, (size_t)D.p_pad));
   CK(dalloc(h, &B.psi, (size_t)D.p_pad));
   CK(dalloc(h, &B.upart, (size_t)D.cb1 * (size_t)n));
-  CK(dalloc(h, &B.qpart, 2 * (size_t)D.rb2 * (size_t)D.p_pad));  // the setup uses two such arrays
+  // The setup uses two arrays of row-panel partials.  The handle keeps both where its
+  // panels of at least 32 rows leave them no larger than one with panels of four;
+  // else the second is given back after the setup.
+  const size_t parts = (size_t)D.rb2 * (size_t)D.p_pad;
+  const int64_t fine = panel_rows_b(n, D.cb2, 4);
+  const bool keep_parts = !flsa && 2 * (int64_t)D.rb2 <= (n + fine - 1) / fine;
+  CK(dalloc(h, &B.qpart, keep_parts ? 2 * parts : parts));
   CK(dalloc(h, &B.pqpart, (size_t)D.gridB));
   CK(dalloc(h, &B.losspart, (size_t)std::max(D.rb2, D.cb2)));
   CK(dalloc(h, &B.penpart, (size_t)D.nblk));
@@ -839,7 +851,13 @@ static flr_status create_impl(flr_ctx ctx, const void* X, flr_dtype x_dtype, int
   if (!flsa) {
     CK(launch_check_finite(Xd, x_dtype, (int64_t)n * D.ldx, flag, h->stream));
     cpart = B.qpart;
-    spart = B.qpart + (size_t)D.rb2 * (size_t)D.p_pad;
+    std::unique_ptr<void, hipError_t (*)(void*)> second(nullptr, hipFree);
+    if (!keep_parts) {
+      void* mem = nullptr;
+      CK(hipMalloc(&mem, parts * sizeof(double)));
+      second.reset(mem);
+    }
+    spart = keep_parts ? B.qpart + parts : static_cast<double*>(second.get());
     CK(launch_setup(D, Xd, yd, cpart, spart, c, s, h->stream));
     CK(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     CK(hipMemcpyAsync(hc.data(), c, (size_t)D.p * sizeof(double), hipMemcpyDeviceToHost, h->stream));

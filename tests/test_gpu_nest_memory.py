@@ -1,4 +1,4 @@
-"""The memory of the nested dense inverses: taken by the first solve that applies
+"""What a handle's memory is charged with.  Nested dense inverses: taken by the first solve that applies
 them and by no other, never a reason to refuse a request or a solve, and given
 back when a server's budget cannot hold it.  Without it a solve applies the
 banded factor: same iterates to the FP64 bar of the parity tests (1e-8 of
@@ -89,4 +89,18 @@ def test_solve_where_the_memory_is_not_free(flr, ctx):
     s = prob.solve(0.3, 0.7, tol=1e-14, **OPTS)
     assert base + 2 ** 29 < prob.footprint < base + 3 * 2 ** 29  # 1184 segments; cut into 128 they took 3.1 GB
     _close(tight.beta, s.beta)
+    prob.close()
+
+
+@pytest.mark.parametrize("n,p", [(1000, 10000), (500, 5000), (200, 1000)])
+def test_setup_scratch_is_not_kept(flr, ctx, n, p):
+    # X, the vectors, the edges and ONE array of X^T u partials: at most 512 / 40 rows of p where the launch target
+    # bounds the row panels (p = 10^4), 512 / 20 at p = 5000, and a panel per four rows anywhere
+    X = np.random.default_rng(1).standard_normal((n, p)).astype(np.float32)
+    prob = flr.Problem(ctx, X, flr.FLR_F32, np.ones(n), flrgen.chain_edges(p), use_tuned=False)
+    pad = (p + 1023) // 1024 * 1024
+    parts = min(-(-512 // (pad // 256)), n // 4) * pad * 8
+    rest = n * pad * 4 + 16 * pad * 8 + 2 * p * 12 + (pad // 1024 + 1) * n * 8 + 65536
+    print("  n=%d p=%d: footprint %d, bound %d" % (n, p, prob.footprint, rest + parts), flush=True)
+    assert prob.footprint <= rest + parts
     prob.close()
