@@ -4,7 +4,8 @@
 // kernels that run in a fixed rotation A, B, C (a hipGraph holds S rounds);
 // when M is banded with bandwidth >= 2 further launches after C apply M^-1: K1
 // to K3 through nested dense inverses (flr_nest.h), or K through its banded
-// Cholesky factor (flr_band.h) where those would need too much memory:
+// Cholesky factor (flr_band.h) where those would need too much memory or M is too
+// ill conditioned for an explicit inverse:
 //   A  row-panel GEMV   u = X v            (v = new CG direction, or the MM iterate)
 //   B  column-panel GEMV q = X^T u (+ M v)  (plus, at an MM boundary: objective
 //                                            partials, reweighting, factorization products)

@@ -29,7 +29,10 @@
 // <= 0), and so is every Schur complement; off the diagonal the sweep only
 // adds terms of one sign, so every entry of the inverses and of W has a
 // relative error of a few ulp given the pivots, as in a Cholesky factorization,
-// also where the weights reach 1/eps.
+// also where the weights reach 1/eps.  The products with the inverse are another
+// matter: entries of its size ||M^-1|| hide its least eigenvalue 1 / ||M|| once the
+// condition number comes near 2^53, where triangular solves still resolve it; such
+// solves keep the band factor (nest_accurate in the engine).
 //
 // Measured (sweeps and factorization in one workgroup before -> here): the 100 x
 // 100 lattice 1153 -> 26 us per PCG step and 10.2 -> 1.1 ms per factorization (the

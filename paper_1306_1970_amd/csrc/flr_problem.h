@@ -26,8 +26,8 @@ struct flr_ctx_s {
   bool own_stream = false;
 };
 
-// Number of rotation rounds captured in one graph (3*S launches, or 4*S with
-// the banded solve; S even keeps the state parity fixed per node).
+// Number of rotation rounds captured in one graph (3 launches each, 4 to 6 with a
+// banded M; an even number keeps the state parity fixed per node).
 static constexpr int kRounds = 16;
 
 struct flr_problem_s {

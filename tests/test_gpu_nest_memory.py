@@ -68,6 +68,33 @@ def test_budget_of_the_banded_factor_is_enough(flr, ctx, q):
     prob.close()
 
 
+def test_slots_take_and_release_while_others_capture(flr, ctx):
+    # four slots at once: fresh handles take the memory, then a small budget makes every one give it back, each
+    # while the other slots capture their rotations; results as on a handle alone
+    q = 34
+    ys = [np.random.default_rng(k).standard_normal(q * q) for k in range(4)]
+    probs = [flr.Problem.flsa(ctx, y, flrgen.lattice_edges(q)) for y in ys]
+    base = [p.footprint for p in probs]
+    o = flr.default_opts(**OPTS)
+    got = {}
+    for name, budget in (("large", 2 ** 34), ("small", sum(base))):
+        srv = flr.flr_server_create(ctx.h, budget, 4)
+        tickets = [flr.flr_server_submit(srv, p.h, 0.3, 0.7, 1e-14, o) for p in probs]
+        betas = [np.zeros(p.p) for p in probs]
+        for t, b in zip(tickets, betas):
+            st, res = flr.flr_server_poll(srv, t, True, b)
+            assert st == flr.FLR_ERR_MAX_ITER
+        flr.flr_server_destroy(srv)
+        got[name] = betas
+        held = [p.footprint > f for p, f in zip(probs, base)]
+        print("  %s budget: inverses held %s" % (name, held), flush=True)
+        assert held == [name == "large"] * 4
+    for p, big, small in zip(probs, got["large"], got["small"]):
+        _close(small, big)
+        assert np.array_equal(p.solve(0.3, 0.7, tol=1e-14, **OPTS).beta, big)
+        p.close()
+
+
 def test_solve_where_the_memory_is_not_free(flr, ctx):
     import torch
 
