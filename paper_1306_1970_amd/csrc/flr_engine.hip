@@ -282,15 +282,16 @@ int auto_preconditioner(flr_problem h, double l1) {
 // Whether an explicit inverse of M is accurate enough to precondition with: its
 // rounding, 2^-53 ||M^-1||, has to stay below its least eigenvalue 1 / ||M||, or the
 // stiff directions (couplings near lambda2 / eps) are lost.  kappa bounds the condition
-// number with the initial iterate's size for |b|.  PCG steps against the band factor's,
-// whose triangular solves do not suffer so: all pairs of 60 the same at kappa = 1e10,
-// 1.3 x at 1e14 (where a step is still 1.6 x faster), 2 x at 1e16, 60 x and numerical
-// failures at 1e18; lattices the same at 1e16, 2 x at 1e18.  eps = 1e-8, |b| = 2:
-// lattices down to lambda1 = 2e-5 lambda2.
+// number with the initial iterate's size for |b|.  PCG steps and time of a call against
+// the band factor's, whose triangular solves do not suffer so: all pairs of 30 the same
+// steps at kappa = 1e13, 1.23 x and 1.00 x the time at 1e15, 3.4 x and 2.0 x at 1e17,
+// 31 x and 13.5 x at 1e18, and numerical failures beyond; all pairs of 60 1.13 x and
+// 0.85 x at 1e15, 11 x and 5.3 x at 1e18; lattices (6 to 24 a side) 1.05 - 1.15 x and
+// 0.31 - 0.69 x at 1e15.  eps = 1e-8, |b| = 2: lattices down to lambda1 = 2e-6 lambda2.
 bool nest_accurate(flr_problem h, double l1, double l2, const flr_solve_opts* o) {
   const double eps = o && o->eps > 0.0 ? o->eps : 1e-8;
   const double kappa = (l1 + 2.0 * (double)h->max_deg * l2) / eps * ((h->beta0 + eps) / l1);
-  return kappa <= 0x1p46;
+  return kappa <= 0x1p50;
 }
 
 // Parameters, warm start and initial state of a solve (solve_begin adds the
