@@ -120,9 +120,10 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
 // (flr_nest.h): the S with the least time for a typical MM iteration, one
 // factorization and 40 applies.  The model, in us: an apply costs its bytes at
 // 4.5 TB/s and 3 (S = 1) or 9 (three launches); a stage 14 (the inversion of the
-// next pivot block) or its tiles at 3.4 us of matrix-core time per CU.  The
-// minimum is flat: twice the stage times (measured, 24 to 31) move S by one or
-// two.  Small orders stay whole (S = 1 up to p of about 1100); 100 x 100 gives
+// next pivot block) or its tiles at 3.4 us of matrix-core time per CU.  Measured are
+// 23 to 31 us for a stage of the separators' matrix and, growing as rows fill, 27 to
+// 59 for the segments' of 100 x 100, 33 to 103 of 128 x 128.  The minimum is flat:
+// twice the stage times move S by one or two.  Small orders stay whole (S = 1 up to p of about 1100); 100 x 100 gives
 // S = 15, 128 x 128 S = 19, p = 2 10^5 with bw = 2 S = 1184.  The separators'
 // right-hand side has to fit the LDS, which ends S; the least time is near the least
 // memory too (p = 2 10^5, bw = 2: 1.05 GB, with S = 128 3.1).  S = 0, the band factor in
