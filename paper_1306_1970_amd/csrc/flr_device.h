@@ -267,7 +267,7 @@ struct Mob {
 // where lambda1 / |b| is above 1e-16 lambda2 / eps no value changes.
 __device__ inline Mob mob_leaf(double alpha, double e) {
   if (!(e > 0.0)) return {0.0, alpha, 0.0, 1.0};  // no coupling: the map is constant
-  alpha = fmax(alpha, 0x1p-53 * e);
+  if (alpha < 0x1p-53 * e) alpha = 0x1p-53 * e;  // not fmax, which would drop a NaN
   if (e >= 1.0) return {alpha / e + 1.0, alpha, 1.0 / e, 1.0};
   return {alpha + e, alpha * e, 1.0, e};
 }
