@@ -123,10 +123,11 @@ Dims choose_dims(int64_t n, int64_t p, int dtype, bool flsa) {
 // next pivot block) or its tiles at 3.4 us of matrix-core time per CU.  Measured are
 // 23 to 31 us for a stage of the separators' matrix and, growing as rows fill, 27 to
 // 59 for the segments' of 100 x 100, 33 to 103 of 128 x 128.  The minimum is flat:
-// twice the stage times move S by one or two.  Small orders stay whole (S = 1 up to p of about 1100); 100 x 100 gives
-// S = 15, 128 x 128 S = 19, p = 2 10^5 with bw = 2 S = 1184.  The separators'
-// right-hand side has to fit the LDS, which ends S; the least time is near the least
-// memory too (p = 2 10^5, bw = 2: 1.05 GB, with S = 128 3.1).  S = 0, the band factor in
+// twice the stage times move S by one or two.  Small orders stay whole (S = 1 up to
+// p of about 1100); 100 x 100 gives S = 15, 128 x 128 S = 19, p = 2 10^5 with bw = 2
+// S = 1184.  The separators' right-hand side has to fit the LDS, which ends S; the
+// least time is near the least memory too (p = 2 10^5, bw = 2: 1.05 GB, with S = 128
+// 3.1).  S = 0, the band factor in
 // one workgroup instead, where the matrices pass 4 GB (the band factor's own
 // limit) or a segment the LDS.
 Nest nest_plan(int64_t p, int64_t bw) {
@@ -326,9 +327,8 @@ flr_status solve_prepare(flr_problem h, double l1, double l2, double tol, const 
     return fail(FLR_ERR_INVALID_ARG, "banded preconditioner: the edge set has bandwidth < 2 or its band is too wide");
   P.jacobi = pre == FLR_PRECOND_JACOBI ? 1 : 0;
   P.band = pre == FLR_PRECOND_BAND ? h->band_w : 0;
-  h->band_mode = !P.band                                                         ? BAND_NONE
-                 : may_nest && nest_accurate(h, l1, l2, o) && nest_ready(h) ? BAND_NEST
-                                                                                 : BAND_FACTOR;
+  h->band_mode = BAND_NONE;
+  if (P.band) h->band_mode = may_nest && nest_accurate(h, l1, l2, o) && nest_ready(h) ? BAND_NEST : BAND_FACTOR;
   P.mixed = o->precision == FLR_PREC_MIXED_FP32 ? 1 : 0;
   HIP_OR_FAIL(hipMemcpyAsync(h->d_prm, h->h_prm, sizeof(Params), hipMemcpyHostToDevice, h->stream));
 
